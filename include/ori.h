@@ -36,10 +36,13 @@
  *  - A context is not thread safe; distinct contexts are independent.
  *  - Supported n: every 1 <= n <= 512.  Each axis is padded to the
  *    shortest planned FFT length L >= 2n - 1 from
- *    {2,4,6,8,10,12,16,20,24,32,40,48,64,80,96,128,192,256,384,512,1024}
+ *    {2,4,6,8,10,12,16,20,24,32,40,48,64,72,80,96,100,108,128,144,160,192,
+ *    200,216,256,288,320,360,384,400,432,512,576,640,720,768,1024}
  *    (the cyclic convolution of length L then holds every offset in
  *    (-n, n): Section 3's zero padding); L = 2n whenever 2n is in the list
- *    (n = 7 uses 16, n = 100 uses 256).  n > 512 gives ORI_ERR_UNSUPPORTED.
+ *    (n = 7 uses 16, n = 100 uses 200).  n > 512 gives ORI_ERR_UNSUPPORTED.
+ *    The workspace is sized for the shortest length of
+ *    {2,4,6,8,10,12,16,20,24,32,40,48,64,80,96,128,192,256,384,512,1024}.
  */
 #ifndef ORI_H
 #define ORI_H

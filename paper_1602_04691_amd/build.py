@@ -4,7 +4,7 @@
 
 Compiles the FFT pass kernels once per supported padded length L
 (``csrc/passes.hip`` with ``-DORI_L=<L>``), the multi-problem passes of the
-short lengths (``csrc/multi_passes.hip``), the auxiliary kernels and the
+short lengths (``csrc/multi_passes.hip``, once per precision and set of lengths), the auxiliary kernels and the
 host runtime, and links ``paper_1602_04691_amd/libori.so``.
 """
 
@@ -44,7 +44,9 @@ def supported_lengths():
 def _sources():
     units = [(os.path.join(CSRC, "passes.hip"), f"passes_L{L}.o", [f"-DORI_L={L}"])
              for L in supported_lengths()]
-    units.append((os.path.join(CSRC, "multi_passes.hip"), "multi_passes.o", []))
+    # the longest compiles first
+    units = [(os.path.join(CSRC, "multi_passes.hip"), f"multi_passes_f{p}_{a}.o",
+              [f"-DORI_MULTI_PREC={p}", f"-DORI_MULTI_ALL={a}"]) for p in (64, 32) for a in (1, 0)] + units
     units.append((os.path.join(CSRC, "aux.hip"), "aux.o", []))
     units.append((os.path.join(CSRC, "physics.hip"), "physics.o", []))
     units.append((os.path.join(CSRC, "ori_api.cpp"), "ori_api.o", ["-x", "hip"]))

@@ -300,6 +300,115 @@ struct Dft<INV, 5, T> {
   }
 };
 
+// Radix R = Q * 3 or Q * 5 with Q = 2 or 4 by the prime-factor map (Good):
+// input (O n1 + Q n2) mod R, output k with k = k1 mod Q and k = k2 mod O, so
+// that the Q-point and O-point butterflies meet no twiddle.  The inputs n1 of
+// one Q-point butterfly lie R / Q apart, so in the half-input form (inputs
+// R / 2 .. R - 1 zero) exactly half of each are zero.
+template <bool INV, int Q, int O, typename T>
+struct DftPfa {
+  static constexpr int R = Q * O;
+  static constexpr int in_index(int n1, int n2) { return (O * n1 + Q * n2) % R; }
+  // the k with k = k1 mod Q and k = k2 mod O (O odd: O = 1 mod 2, and mod 4
+  // its inverse is itself; Q inverts mod 3 and 5 as below)
+  static constexpr int inv_q = O == 3 ? (Q == 2 ? 2 : 1) : (Q == 2 ? 3 : 4);
+  static constexpr int out_index(int k1, int k2) { return (O * (O % Q) * k1 + Q * inv_q * k2) % R; }
+  static_assert((Q * inv_q) % O == 1 && (O * (O % Q)) % Q == 1, "prime-factor map");
+  // the O-point butterflies over the rows w[k1 * O + .] of the Q-point results
+  __device__ __forceinline__ static void finish(cx<T>* w, cx<T>* v) {
+#pragma unroll
+    for (int k1 = 0; k1 < Q; ++k1) {
+      Dft<INV, O, T>::run(w + k1 * O);
+#pragma unroll
+      for (int k2 = 0; k2 < O; ++k2) v[out_index(k1, k2)] = w[k1 * O + k2];
+    }
+  }
+  __device__ __forceinline__ static void run(cx<T>* v) {
+    cx<T> w[R];
+#pragma unroll
+    for (int n2 = 0; n2 < O; ++n2) {
+      cx<T> c[Q];
+#pragma unroll
+      for (int n1 = 0; n1 < Q; ++n1) c[n1] = v[in_index(n1, n2)];
+      Dft<INV, Q, T>::run(c);
+#pragma unroll
+      for (int k1 = 0; k1 < Q; ++k1) w[k1 * O + n2] = c[k1];
+    }
+    finish(w, v);
+  }
+  // inputs R / 2 .. R - 1 are zero.  Of the Q inputs n1 of a butterfly those
+  // with in_index < R / 2 remain: s = first_nonzero and, for Q = 4, the next
+  // one (mod Q).  Counted from s they are the half-input butterfly, and
+  // output k1 then takes the factor exp(-+2 pi i k1 s / Q).
+  __device__ __forceinline__ static void run_half(cx<T>* v) {
+    cx<T> w[R];
+#pragma unroll
+    for (int n2 = 0; n2 < O; ++n2) {
+      const int s = first_nonzero(n2);
+      cx<T> c[Q] = {};
+      c[0] = v[in_index(s, n2)];
+      if (Q == 4) c[1] = v[in_index((s + 1) % Q, n2)];
+      Dft<INV, Q, T>::run_half(c);
+#pragma unroll
+      for (int k1 = 0; k1 < Q; ++k1) {
+        const int turn = (4 / Q * k1 * s) % 4;  // quarter turns
+        cx<T> y = c[k1];
+        if (turn == 1) y = mul_w4<INV>(y);
+        if (turn == 2) y = cx<T>{-y.re, -y.im};
+        if (turn == 3) y = mul_w4<!INV>(y);
+        w[k1 * O + n2] = y;
+      }
+    }
+    finish(w, v);
+  }
+  static constexpr int first_nonzero(int n2) {
+    int s = 0;
+    for (int n1 = Q - 1; n1 >= 0; --n1)
+      if (in_index(n1, n2) < R / 2 && in_index((n1 + Q - 1) % Q, n2) >= R / 2) s = n1;
+    return s;
+  }
+};
+
+template <bool INV, typename T>
+struct Dft<INV, 6, T> : DftPfa<INV, 2, 3, T> {};
+template <bool INV, typename T>
+struct Dft<INV, 10, T> : DftPfa<INV, 2, 5, T> {};
+template <bool INV, typename T>
+struct Dft<INV, 12, T> : DftPfa<INV, 4, 3, T> {};
+
+// Radix 9 as 3 x 3: input 3 n1 + n2, output k1 + 3 k2, factors
+// exp(-+2 pi i n2 k1 / 9) between.
+template <bool INV, typename T>
+struct Dft<INV, 9, T> {
+  __device__ __forceinline__ static cx<T> rot(cx<T> a, double c, double s) {
+    const T ct = static_cast<T>(c), st = static_cast<T>(INV ? s : -s);
+    return {fmadd(a.re, ct, -(a.im * st)), fmadd(a.re, st, a.im * ct)};
+  }
+  __device__ __forceinline__ static void run(cx<T>* v) {
+    constexpr double C1 = 0.76604444311897803520, S1 = 0.64278760968653932632;  // 2 pi / 9
+    constexpr double C2 = 0.17364817766693034885, S2 = 0.98480775301220805937;  // 4 pi / 9
+    constexpr double C4 = -0.93969262078590838405, S4 = 0.34202014332566873304;  // 8 pi / 9
+    cx<T> w[9];  // [k1][n2]
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+      cx<T> c[3] = {v[n2], v[3 + n2], v[6 + n2]};
+      Dft<INV, 3, T>::run(c);
+#pragma unroll
+      for (int k1 = 0; k1 < 3; ++k1) w[k1 * 3 + n2] = c[k1];
+    }
+    w[4] = rot(w[4], C1, S1);
+    w[5] = rot(w[5], C2, S2);
+    w[7] = rot(w[7], C2, S2);
+    w[8] = rot(w[8], C4, S4);
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) {
+      Dft<INV, 3, T>::run(w + 3 * k1);
+#pragma unroll
+      for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = w[3 * k1 + k2];
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Stage bookkeeping
 // ---------------------------------------------------------------------------
@@ -319,11 +428,26 @@ struct Stages {
   static constexpr bool radices_ok() {
     for (int s = 0; s < NS; ++s) {
       int r = plan.r[s];
-      if (r != 2 && r != 3 && r != 4 && r != 5 && r != 8 && r != 16) return false;
+      if (r != 2 && r != 3 && r != 4 && r != 5 && r != 6 && (r < 8 || r > 10) && r != 12 && r != 16) return false;
     }
     return true;
   }
-  static_assert(NS > 0 && ns(NS) == L && radices_ok(), "plan must factor L into radices 2, 3, 4, 5, 8, 16");
+  static_assert(NS > 0 && ns(NS) == L && radices_ok(), "plan must factor L into radices 2..6, 8, 9, 10, 12, 16");
+  // Whether the position of every element a thread touches in LDS splits into
+  // its own padded position plus a compile-time offset (LdsPencil::at): the
+  // writes of stage s lie ns(s) apart, its reads L / radix(s).
+  static constexpr bool write_splits(int s) {
+    const int R = radix(s);
+    return ns(s) % 8 == 0 || (ns(s) == 1 && (R & (R - 1)) == 0);
+  }
+  static constexpr bool read_splits(int s) { return L / radix(s) % 8 == 0; }
+  static constexpr bool pad_splits() {
+    for (int s = 0; s < NS; ++s) {
+      if (s + 1 < NS && !write_splits(s)) return false;
+      if (s > 0 && !read_splits(s)) return false;
+    }
+    return true;
+  }
   // Largest twiddle table index any stage reads: the powers r = 1, 2, 4, 8
   // below R of w^(k TS), k < ns(s), TS = L / (ns(s) R).  Below L/2 when every
   // radix is a power of two, so a table staged in LDS can stop there.
@@ -344,7 +468,7 @@ struct Stages {
 // pencils element by element (element e at base[e * es], es = NP): every
 // LDS access of a wavefront is then a run of NP consecutive slots.  Contiguous
 // passes keep each pencil in one row with one padding slot after every 8
-// elements (element e at base[e + e / 8]), which breaks the power-of-two
+// elements (element e at base[e + e / 8], pad = 1), which breaks the power-of-two
 // strides of the Stockham writes across the LDS banks.
 //
 // Narrow interleaves (NP pencils of fewer than 128 bytes per element row)
@@ -369,14 +493,12 @@ struct LdsPencil {
   // and every access of a butterfly shares one address register.
   template <int C, bool SPLIT>
   __device__ __forceinline__ cx<T>& at(int b) const {
-    if (es && !pad) return base[(b + C) * es];
+    if (!pad) return base[(b + C) * es];
     const int row = SPLIT ? b + (b >> 3) + (C + (C >> 3)) : (b + C) + ((b + C) >> 3);
-    return es ? base[row * es] : base[row];
+    return base[row * es];
   }
 };
 
-// LDS slots of one padded contiguous pencil row
-constexpr int padded_row(int L) { return L + L / 8; }
 // LDS rows of an interleave of length L, with or without the padding rows
 constexpr int interleave_rows(int L, bool pad) { return pad ? L + L / 8 : L; }
 
@@ -401,11 +523,15 @@ struct Regs {
 // A radix-8 stage with twiddles runs Dft<8>::run_tw, which uses w, w^2, w^4
 // and w exp(-2 pi i/8): the last is a table entry in mode 1 (entry
 // k TS + L/8 of the length-L table) and a product by a constant otherwise.
-template <typename T, int L, bool INV, int TP = threads_per_pencil(L), int PV = 0, int TWM = 0>
+// IDLE: the workgroup has lanes beyond NP * TPP (block_threads in plan.h);
+// they pass a bt no smaller than every butterfly count and own no butterfly.
+template <typename T, int L, bool INV, int TP = threads_per_pencil(L), int PV = 0, int TWM = 0, bool IDLE = false>
 struct Engine {
   using St = Stages<L, INV, TP, PV>;
   static constexpr int NS = St::NS;
   static constexpr int TPP = St::TPP;
+  // whether a thread's butterfly index may lie beyond the stage's count
+  static constexpr bool ragged(int s) { return IDLE || St::nbf(s) % TPP != 0; }
 
   // Stage-major twiddle table: stage s >= 1 holds w^(r k TS) for the powers
   // r it reads (TWM 1: r = 1..R-1, or for R = 8 the powers 1, 2, 4 and then
@@ -477,7 +603,7 @@ struct Engine {
 #pragma unroll
     for (int i = 0; i < St::cnt(s); ++i) {
       const int b = bt + i * TPP;
-      if (St::nbf(s) % TPP != 0 && b >= St::nbf(s)) continue;
+      if (ragged(s) && b >= St::nbf(s)) continue;
       if constexpr (NSs > 1 && R == 8) {
         const int k = b % NSs;
         cx<T> w1, w2, w4, w1w;
@@ -556,12 +682,12 @@ struct Engine {
 #pragma unroll
     for (int i = 0; i < St::cnt(s); ++i) {
       const int b = bt + i * TPP;
-      if (St::nbf(s) % TPP != 0 && b >= St::nbf(s)) continue;
+      if (ragged(s) && b >= St::nbf(s)) continue;
       const int k = b % NSs;
       const int base = (b - k) * R + k;
       // (base + j NSs) / 8 splits when NSs is a multiple of 8, or in the
       // first stage (NSs = 1, base = b R) for a power-of-two R
-      constexpr bool SPLIT = NSs % 8 == 0 || (NSs == 1 && (R & (R - 1)) == 0);
+      constexpr bool SPLIT = St::write_splits(s);
       unroll<R>([&](auto J) {
         constexpr int j = decltype(J)::value;
         p.template at<j * NSs, SPLIT>(base) = g.v[i][j];
@@ -577,10 +703,10 @@ struct Engine {
 #pragma unroll
     for (int i = 0; i < St::cnt(s); ++i) {
       const int b = bt + i * TPP;
-      if (St::nbf(s) % TPP != 0 && b >= St::nbf(s)) continue;
+      if (ragged(s) && b >= St::nbf(s)) continue;
       unroll<R>([&](auto J) {
         constexpr int r = decltype(J)::value;
-        g.v[i][r] = p.template at<r * STRIDE, STRIDE % 8 == 0>(b);
+        g.v[i][r] = p.template at<r * STRIDE, St::read_splits(s)>(b);
       });
     }
   }
@@ -595,7 +721,7 @@ struct Engine {
 #pragma unroll
     for (int i = 0; i < St::cnt(0); ++i) {
       const int b = bt + i * TPP;
-      if (St::nbf(0) % TPP != 0 && b >= St::nbf(0)) continue;
+      if (ragged(0) && b >= St::nbf(0)) continue;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (SKIP && r >= R / 2) {
@@ -606,49 +732,6 @@ struct Engine {
         } else {
           g.v[i][r] = load(b + r * STRIDE);
         }
-      }
-    }
-  }
-
-  // The same loads with the index of each value in the thread's registers:
-  // load(slot, e), slot = i * R0 + r (a compile-time constant once unrolled).
-  template <bool HALF_IN, class Load>
-  __device__ __forceinline__ static void load_first_slots(RegsOf<0>& g, int bt, Load&& load) {
-    constexpr int R = St::radix(0);
-    constexpr int STRIDE = L / R;
-    constexpr bool SKIP = HALF_IN && (R % 2 == 0);
-#pragma unroll
-    for (int i = 0; i < St::cnt(0); ++i) {
-      const int b = bt + i * TPP;
-      if (St::nbf(0) % TPP != 0 && b >= St::nbf(0)) continue;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (SKIP && r >= R / 2) {
-          g.v[i][r] = cx<T>{};
-        } else if (HALF_IN && !SKIP) {
-          const int e = b + r * STRIDE;
-          g.v[i][r] = e < L / 2 ? load(i * R + r, e) : cx<T>{};
-        } else {
-          g.v[i][r] = load(i * R + r, b + r * STRIDE);
-        }
-      }
-    }
-  }
-
-  // Every element index e that load_first<HALF_IN> reads, with its slot:
-  // f(slot, e) (slots as in load_first_slots).
-  template <bool HALF_IN, class F>
-  __device__ __forceinline__ static void first_slots(int bt, F&& f) {
-    constexpr int R = St::radix(0);
-    constexpr int STRIDE = L / R;
-#pragma unroll
-    for (int i = 0; i < St::cnt(0); ++i) {
-      const int b = bt + i * TPP;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int e = b + r * STRIDE;
-        if (HALF_IN && (R % 2 == 0) && r >= R / 2) continue;
-        f(i * R + r, e);
       }
     }
   }
@@ -665,7 +748,7 @@ struct Engine {
 #pragma unroll
     for (int i = 0; i < St::cnt(s); ++i) {
       const int b = bt + i * TPP;
-      if (St::nbf(s) % TPP != 0 && b >= St::nbf(s)) continue;
+      if (ragged(s) && b >= St::nbf(s)) continue;
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         const int e = b + j * STRIDE;
@@ -677,63 +760,28 @@ struct Engine {
     }
   }
 
-  // The same stores with the slot of each value: store(slot, e, value),
-  // slot = i * R_last + j.
-  template <int KEEP, class Store>
-  __device__ __forceinline__ static void store_last_slots(const RegsOf<NS - 1>& g, int bt, Store&& store) {
-    constexpr int s = NS - 1;
-    constexpr int R = St::radix(s);
-    constexpr int STRIDE = L / R;
-#pragma unroll
-    for (int i = 0; i < St::cnt(s); ++i) {
-      const int b = bt + i * TPP;
-      if (St::nbf(s) % TPP != 0 && b >= St::nbf(s)) continue;
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        const int e = b + j * STRIDE;
-        if (KEEP == KEEP_HALF && (R % 2 == 0) && j >= R / 2) continue;
-        if (KEEP == KEEP_HALF && e >= L / 2) continue;
-        if (KEEP == KEEP_HALF1 && e > L / 2) continue;
-        store(i * R + j, e, g.v[i][j]);
-      }
-    }
-  }
-
-  // Every element index e that store_last<KEEP> may write (bounds on b
-  // aside), with its slot: f(slot, e).
-  template <int KEEP, class F>
-  __device__ __forceinline__ static void last_slots(int bt, F&& f) {
-    constexpr int s = NS - 1;
-    constexpr int R = St::radix(s);
-    constexpr int STRIDE = L / R;
-#pragma unroll
-    for (int i = 0; i < St::cnt(s); ++i) {
-      const int b = bt + i * TPP;
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        if (KEEP == KEEP_HALF && (R % 2 == 0) && j >= R / 2) continue;
-        f(i * R + j, b + j * STRIDE);
-      }
-    }
-  }
-
   // Run stages s..NS-1 starting from inputs already in LDS; hand the last
-  // stage's outputs (natural order, element b + j L/R) to fin(regs).
-  template <int s, class Fin>
-  __device__ __forceinline__ static void run_from_lds(int bt, LdsPencil<T> p, const cx<T>* __restrict__ tw,
-                                                      Fin&& fin) {
+  // stage's outputs (natural order, element b + j L/R) to fin(regs).  pre()
+  // runs before the last stage, while its inputs are exchanged.
+  template <int s, class Fin, class Pre>
+  __device__ __forceinline__ static void run_from_lds(int bt, LdsPencil<T> p, const cx<T>* __restrict__ tw, Fin&& fin,
+                                                      Pre&& pre) {
     RegsOf<s> g;
     read_lds<s>(g, bt, p);
     __syncthreads();
     compute<s, false>(g, bt, tw);
     if constexpr (s + 1 < NS) {
       write_lds<s>(g, bt, p);
+      if constexpr (s + 2 == NS) pre();
       __syncthreads();
-      run_from_lds<s + 1>(bt, p, tw, fin);
+      run_from_lds<s + 1>(bt, p, tw, fin, pre);
     } else {
       fin(g);
     }
   }
+  struct NoPre {
+    __device__ __forceinline__ void operator()() const {}
+  };
 
   // The whole transform of the elementwise product of g0 and sc (both laid
   // out as stage 0's registers): for radix 8 the products are folded into
@@ -745,7 +793,7 @@ struct Engine {
 #pragma unroll
     for (int i = 0; i < St::cnt(0); ++i) {
       const int b = bt + i * TPP;
-      if (St::nbf(0) % TPP != 0 && b >= St::nbf(0)) continue;
+      if (ragged(0) && b >= St::nbf(0)) continue;
       if constexpr (R == 8) {
         Dft<INV, 8, T>::run_scaled(g0.v[i], sc.v[i]);
       } else {
@@ -757,22 +805,24 @@ struct Engine {
     if constexpr (NS > 1) {
       write_lds<0>(g0, bt, p);
       __syncthreads();
-      run_from_lds<1>(bt, p, tw, fin);
+      run_from_lds<1>(bt, p, tw, fin, NoPre{});
     } else {
       fin(g0);
     }
   }
 
   // Whole transform: stage 0 from registers g0 (already loaded), the rest
-  // through LDS; fin(regs of the last stage).
-  template <bool HALF_IN, class Fin>
-  __device__ __forceinline__ static void run(RegsOf<0>& g0, int bt, LdsPencil<T> p,
-                                             const cx<T>* __restrict__ tw, Fin&& fin) {
+  // through LDS; pre() before the last stage, fin(regs of the last stage).
+  template <bool HALF_IN, class Fin, class Pre = NoPre>
+  __device__ __forceinline__ static void run(RegsOf<0>& g0, int bt, LdsPencil<T> p, const cx<T>* __restrict__ tw,
+                                             Fin&& fin, Pre&& pre = Pre{}) {
+    if constexpr (NS == 1) pre();
     compute<0, HALF_IN>(g0, bt, tw);
     if constexpr (NS > 1) {
       write_lds<0>(g0, bt, p);
+      if constexpr (NS == 2) pre();
       __syncthreads();
-      run_from_lds<1>(bt, p, tw, fin);
+      run_from_lds<1>(bt, p, tw, fin, pre);
     } else {
       fin(g0);
     }

@@ -160,6 +160,8 @@ struct LengthKernels {
   int64_t (*strided_blocks)(int fprec, int np_sel, int64_t n_outer, int64_t C);
   int64_t (*zpass_blocks)(int fprec, int np_sel);
   hipError_t (*spectrum)(const SpectrumArgs&, hipStream_t);
+  // largest i1 block (log2) that the Z pass addresses with per-lane offsets
+  int (*z_align)(int fprec);
 };
 
 const LengthKernels* kernels_for_length(int L);
@@ -198,19 +200,29 @@ constexpr bool multi_length(int L) { return L >= 8 && L <= 256 && radix_plan(L).
 // default layout up to L = 256).  A problem whose layout differs runs its
 // own launches.
 constexpr int kMultiZNarrow[2] = {0, 1};  // [PREC_F64, PREC_F32]
-// Workgroup size of pass `pass` (MultiPass) at length L in precision prec,
-// or 0 if L has no multi-problem bodies.
-int multi_pass_threads(int L, int prec, int pass);
-// whether the Z pass of that length addresses its tiles with scalar offsets
-// at i1 block 2^e_lg (MultiProblem::soff, as the single-problem launch decides)
-bool multi_z_soff(int L, int prec, int e_lg);
-// LDS bytes of that pass and length
-int multi_pass_smem(int L, int prec, int pass);
-// tab: device array of np problems (first_block ascending), blocks = the
-// sum of their nblocks; threads and smem = the largest multi_pass_threads
-// and multi_pass_smem of them.
-hipError_t launch_multi_pass(int prec, int pass, const MultiProblem* tab, int32_t np, int64_t blocks, int threads,
-                             int smem, hipStream_t st);
+// The multi-problem launches of one precision and set of lengths
+// (multi_passes.hip): every multi_length, or the reserved ones alone.
+struct MultiKernels {
+  // workgroup size of pass `pass` (MultiPass) at length L, or 0 if L has no
+  // multi-problem bodies, and its LDS bytes
+  int (*threads)(int L, int pass);
+  int (*smem)(int L, int pass);
+  // whether the Z pass of that length addresses its tiles with scalar offsets
+  // at i1 block 2^e_lg (MultiProblem::soff, as the single-problem launch decides)
+  bool (*z_soff)(int L, int e_lg);
+  // tab: device array of np problems (first_block ascending), blocks = the
+  // sum of their nblocks; threads and smem = the largest of theirs
+  hipError_t (*launch)(int pass, const MultiProblem* tab, int32_t np, int64_t blocks, int threads, int smem,
+                       hipStream_t st);
+};
+const MultiKernels* multi_kernels_f64_0();
+const MultiKernels* multi_kernels_f64_1();
+const MultiKernels* multi_kernels_f32_0();
+const MultiKernels* multi_kernels_f32_1();
+inline const MultiKernels* multi_kernels(int prec, bool all) {
+  if (prec == PREC_F64) return all ? multi_kernels_f64_1() : multi_kernels_f64_0();
+  return all ? multi_kernels_f32_1() : multi_kernels_f32_0();
+}
 
 // finalisation of several problems: problem p's right-hand sides are
 // workgroups [first_block, first_block + nrhs) of the launch

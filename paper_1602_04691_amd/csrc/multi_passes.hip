@@ -3,11 +3,16 @@
 // Every length of multi_length() has its pass bodies compiled here, in a
 // namespace of its own, from the same source as its single-problem kernels
 // (pass_bodies.inc), with the tile shape of kernels.h; a launch runs each
-// problem's workgroups on its own length's body.
+// problem's workgroups on its own length's body.  Compiled once per precision
+// and set of lengths (-DORI_MULTI_PREC=64 or 32, -DORI_MULTI_ALL=0 or 1).
 #include "fft_engine.h"
 #include "kernels.h"
 #include "launch.h"
 #include "pass_common.h"
+
+#if !defined(ORI_MULTI_PREC) || (ORI_MULTI_PREC != 64 && ORI_MULTI_PREC != 32) || !defined(ORI_MULTI_ALL)
+#error "compile with -DORI_MULTI_PREC=64 and 32, -DORI_MULTI_ALL=0 and 1"
+#endif
 
 namespace ori {
 
@@ -101,8 +106,62 @@ constexpr int L = 256;
 #include "multi_len.inc"
 }  // namespace ml256
 
-// every length with multi-problem bodies (multi_length in kernels.h)
-#define ORI_MULTI_LENGTHS(X) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96) X(128) X(192) X(256)
+#if ORI_MULTI_ALL
+namespace ml72 {
+constexpr int L = 72;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml72
+
+namespace ml100 {
+constexpr int L = 100;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml100
+
+namespace ml108 {
+constexpr int L = 108;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml108
+
+namespace ml144 {
+constexpr int L = 144;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml144
+
+namespace ml160 {
+constexpr int L = 160;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml160
+
+namespace ml200 {
+constexpr int L = 200;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml200
+
+namespace ml216 {
+constexpr int L = 216;
+#include "pass_bodies.inc"
+#include "multi_len.inc"
+}  // namespace ml216
+#endif
+
+// The lengths of this translation unit: every length with multi-problem
+// bodies (multi_length in kernels.h), or the reserved ones alone.  The
+// radix 10 and 12 stages of the lengths between them need more registers
+// (complex128 F2 104 instead of 80), which every workgroup of a launch
+// pays for, so a set of problems without such a length runs kernels
+// without their bodies (n = 19 and 83 in complex128: 3.0 vs 3.5 ms).
+#define ORI_MULTI_RESERVED(X) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96) X(128) X(192) X(256)
+#if ORI_MULTI_ALL
+#define ORI_MULTI_LENGTHS(X) ORI_MULTI_RESERVED(X) X(72) X(100) X(108) X(144) X(160) X(200) X(216)
+#else
+#define ORI_MULTI_LENGTHS(X) ORI_MULTI_RESERVED(X)
+#endif
 
 namespace {
 
@@ -157,6 +216,7 @@ hipError_t launch_t(const MultiProblem* tab, int32_t np, int64_t blocks, int thr
 template <typename T>
 hipError_t launch_prec(int pass, const MultiProblem* tab, int32_t np, int64_t blocks, int threads, int smem,
                        hipStream_t st) {
+  if (np < 1 || blocks < 1) return hipErrorInvalidValue;
   switch (pass) {
     case MP_F1: return launch_t<T, MP_F1>(tab, np, blocks, threads, smem, st);
     case MP_F2: return launch_t<T, MP_F2>(tab, np, blocks, threads, smem, st);
@@ -229,23 +289,14 @@ bool soff_prec(int L, int e_lg) {
 
 }  // namespace
 
-int multi_pass_threads(int L, int prec, int pass) {
-  return prec == PREC_F64 ? threads_prec<double>(L, pass) : threads_prec<float>(L, pass);
-}
+#define ORI_CAT2(a, b, c, d) a##b##c##d
+#define ORI_CAT(a, b, c, d) ORI_CAT2(a, b, c, d)
+#define ORI_MULTI_TABLE ORI_CAT(multi_kernels_f, ORI_MULTI_PREC, _, ORI_MULTI_ALL)
+using MT = std::conditional_t<ORI_MULTI_PREC == 64, double, float>;
 
-int multi_pass_smem(int L, int prec, int pass) {
-  return prec == PREC_F64 ? smem_prec<double>(L, pass) : smem_prec<float>(L, pass);
-}
-
-bool multi_z_soff(int L, int prec, int e_lg) {
-  return prec == PREC_F64 ? soff_prec<double>(L, e_lg) : soff_prec<float>(L, e_lg);
-}
-
-hipError_t launch_multi_pass(int prec, int pass, const MultiProblem* tab, int32_t np, int64_t blocks, int threads,
-                             int smem, hipStream_t st) {
-  if (np < 1 || blocks < 1) return hipErrorInvalidValue;
-  return prec == PREC_F64 ? launch_prec<double>(pass, tab, np, blocks, threads, smem, st)
-                          : launch_prec<float>(pass, tab, np, blocks, threads, smem, st);
+const MultiKernels* ORI_MULTI_TABLE() {
+  static const MultiKernels k = {threads_prec<MT>, smem_prec<MT>, soff_prec<MT>, launch_prec<MT>};
+  return &k;
 }
 
 }  // namespace ori

@@ -386,6 +386,17 @@ int64_t padded_length(int64_t n) {
   return best;
 }
 
+// The padded length a context's workspace is sized for (plan.h,
+// ORI_FOR_EACH_RESERVED_L), no shorter than padded_length(n).
+int64_t reserved_length_for(int64_t n) {
+  int64_t best = 0;
+#define ORI_PICK(Lc) \
+  if ((Lc) >= 2 * n - 1 && (best == 0 || (Lc) < best)) best = (Lc);
+  ORI_FOR_EACH_RESERVED_L(ORI_PICK)
+#undef ORI_PICK
+  return best;
+}
+
 ori_status check_grid(const ori_grid* g, int64_t* L_out) {
   if (!g) return set_err(nullptr, ORI_ERR_INVALID_ARG, "grid is NULL");
   if (g->n < 1) return set_err(nullptr, ORI_ERR_INVALID_ARG, "n = %lld must be >= 1", (long long)g->n);
@@ -412,7 +423,7 @@ struct Layout {
 // largest reducing grid: I1 (at most n*n workgroups per right-hand side) and
 // the reduction kernels (red_blocks(P), update_blocks(P, prec) per right-hand side).
 Layout layout_for(int64_t n, int64_t nrhs, int provision) {
-  const int64_t L = padded_length(n);
+  const int64_t L = reserved_length_for(n);
   const int64_t P = n * n * n, kp = L / 2 + 1;
   const bool mixed = provision & ORI_PROVISION_MIXED;
   Layout l{};
@@ -785,6 +796,7 @@ using Members = std::vector<ori_ctx>;
 struct MultiSet {
   Members members;
   int prec = 0;
+  const MultiKernels* kernels = nullptr;
   void* dev = nullptr;  // every table, one block (device_pool)
   size_t dev_bytes = 0;
   int device = 0;
@@ -833,6 +845,7 @@ bool multi_ok(const Members& ms, int prec) {
     if (!multi_length(static_cast<int>(c->L)) || c->nrhs != 1 || c->prof || c->check_guards || k.np_sel != 0 ||
         k.zpf != 0 || k.zplan != 0 || k.z_np != kMultiZNarrow[f])
       return false;
+    if (!reserved_length(static_cast<int>(c->L)) && k.blk_lg > c->K->z_align(prec)) return false;
   }
   return true;
 }
@@ -857,6 +870,9 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
   std::vector<MultiFin> fmu(M), frho(M);
   std::vector<MultiUpd> up(M);
   int64_t first[MP_NPASS] = {};
+  bool all = false;  // some length lies between the reserved ones
+  for (ori_ctx c : act) all = all || !reserved_length(static_cast<int>(c->L));
+  const MultiKernels* mk = ms->kernels = multi_kernels(prec, all);
   for (size_t i = 0; i < M; ++i) {
     ori_ctx c = act[i];
     const PrecVecs v = vecs(c, prec);
@@ -876,7 +892,7 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
       e.nblocks = pa.blocks[p];
       e.L = L;
       e.ex = 2 * c->n == c->L;
-      e.soff = multi_z_soff(L, prec, pa.z.e_lg);
+      e.soff = mk->z_soff(L, pa.z.e_lg);
       if (p == MP_F1) e.a.f1 = pa.f1;
       if (p == MP_F2) e.a.s = pa.f2;
       if (p == MP_Z) e.a.z = pa.z;
@@ -888,8 +904,8 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
         tp[MP_NPASS].push_back(e);
       }
       first[p] += pa.blocks[p];
-      ms->threads[p] = std::max(ms->threads[p], multi_pass_threads(L, prec, p));
-      ms->smem[p] = std::max(ms->smem[p], multi_pass_smem(L, prec, p));
+      ms->threads[p] = std::max(ms->threads[p], mk->threads(L, p));
+      ms->smem[p] = std::max(ms->smem[p], mk->smem(L, p));
       ms->blocks[p] = first[p];
     }
     const int64_t ub = update_blocks(c->P, prec);
@@ -960,7 +976,7 @@ ori_status multi_iteration(const MultiSet& m, bool first, hipStream_t st) {
   const int32_t np = static_cast<int32_t>(m.members.size());
   for (int p = 0; p < MP_NPASS; ++p) {
     const MultiProblem* tab = (p == MP_F1 && first) ? m.f1_first : m.pass[p];
-    ORI_HIP(c0, launch_multi_pass(m.prec, p, tab, np, m.blocks[p], m.threads[p], m.smem[p], st));
+    ORI_HIP(c0, m.kernels->launch(p, tab, np, m.blocks[p], m.threads[p], m.smem[p], st));
   }
   ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, st));
   ORI_HIP(c0, launch_multi_update(m.prec, m.upd, np, m.upd_blocks, st));
@@ -1177,10 +1193,13 @@ std::vector<double> true_residual_orig_read(ori_ctx c) {
 // complex64 at every length (at L = 512 its wide workgroup of 16 wavefronts
 // fits once per CU, the narrow one three times) and complex128 from L = 512
 // on (0.57 vs 0.65 ms at n = 256, while wide tiles win at L = 256).
-bool valid_knobs(int64_t n, int64_t L, const Knobs& k) {
+// zplan 1 is valid where the reserved length has a second plan; a length
+// between the reserved ones runs its one plan for either value.
+bool valid_knobs(int64_t n, const Knobs& k) {
+  const int L = static_cast<int>(reserved_length_for(n));
   return k.blk_lg >= 0 && k.blk_lg <= 6 && n % (int64_t{1} << k.blk_lg) == 0 && (k.np_sel == 0 || k.np_sel == 1) &&
          (k.zpf == 0 || k.zpf == 1) && (k.z_np == 0 || k.z_np == 1) &&
-         (k.zplan == 0 || (k.zplan == 1 && has_plan_variant(static_cast<int>(L))));
+         (k.zplan == 0 || (k.zplan == 1 && has_plan_variant(L)));
 }
 
 // The Z pass's radix plan by default: the alternative (16 x 8 x 8) for the
@@ -1188,12 +1207,37 @@ bool valid_knobs(int64_t n, int64_t L, const Knobs& k) {
 // default.
 int default_zplan(int64_t L, int f) { return (L == 1024 && f == 0) ? 1 : 0; }
 
+// The i1 block of B by default: 16 rows up to L = 384; then as measured (one
+// product, blocks 2^2 vs 2^4 in complex128 and 2^3 vs 2^4 in complex64:
+// 1.51 vs 1.58 ms and 0.88 vs 0.89 ms at n = 256), and the largest from L =
+// 768 on, whose rows lie 9 MB and more apart (n = 512: complex64 Z 3.69 vs
+// 4.16 ms, complex128 F2 2.62 vs 2.76 ms).  The lengths between the
+// reserved ones stay within the Z pass's per-lane addressing (L = 720:
+// elements 90 rows apart, blocks of two).
+int default_blk_lg(ori_ctx c, int f) {
+  const bool reserved = reserved_length(static_cast<int>(c->L));
+  int lg = c->L >= 768 ? 6 : c->L > 384 ? (f ? 3 : 2) : 4;
+  if (!reserved) lg = std::min(lg, c->K->z_align(f ? PREC_F32 : PREC_F64));
+  while (lg > 0 && c->n % (int64_t{1} << lg) != 0) --lg;
+  return lg;
+}
+
+// Z tiles by default.  The lengths between the reserved ones from L = 576 on:
+// complex128 wide (128-byte rows; n = 360 5.24 vs 6.37 ms, n = 320 3.65 vs
+// 3.73 ms), complex64 narrow where narrow tiles are whole wavefronts (n =
+// 320 2.06 vs 2.35 ms, but n = 360 3.10 vs 2.88 ms).
+int default_znarrow(ori_ctx c, int f) {
+  const int L = static_cast<int>(c->L);
+  if (reserved_length(L) || L < 576) return (f == 1 || L >= 512) ? 1 : 0;
+  return f == 1 && 4 * threads_per_pencil(L) % 64 == 0 ? 1 : 0;
+}
+
 void choose_layout(ori_ctx c) {
   for (int f = 0; f < 2; ++f) {
     Knobs k;
-    k.z_np = (f == 1 || c->L >= 512) ? 1 : 0;
+    k.z_np = default_znarrow(c, f);
     k.zplan = default_zplan(c->L, f);
-    while (k.blk_lg > 0 && (c->n % (int64_t{1} << k.blk_lg)) != 0) --k.blk_lg;
+    k.blk_lg = default_blk_lg(c, f);
     c->knob[f] = k;
   }
   {
@@ -1209,7 +1253,7 @@ void choose_layout(ori_ctx c) {
     if (const char* e = std::getenv("ORI_TUNE_NP")) k.np_sel = std::atoi(e) ? 1 : 0;
     if (const char* e = std::getenv("ORI_TUNE_ZPF")) k.zpf = std::atoi(e) ? 1 : 0;
     if (const char* e = std::getenv("ORI_TUNE_ZNP")) k.z_np = std::atoi(e) ? 1 : 0;
-    if (const char* e = std::getenv("ORI_TUNE_ZPLAN")) k.zplan = std::atoi(e) && has_plan_variant(c->L) ? 1 : 0;
+    if (const char* e = std::getenv("ORI_TUNE_ZPLAN")) k.zplan = std::atoi(e) && has_plan_variant(static_cast<int>(reserved_length_for(c->n))) ? 1 : 0;
     if (k.blk_lg < 0) k.blk_lg = 0;
     if (k.blk_lg > 6) k.blk_lg = 6;
     while (k.blk_lg > 0 && (c->n % (int64_t{1} << k.blk_lg)) != 0) --k.blk_lg;
@@ -1625,8 +1669,8 @@ struct StaticLayout {
 // The context layout_for gives one right-hand side, restricted to what the
 // product needs: the arena (A and B, also the spectrum passes' octant
 // scratch), the octant and its complex64 copy, and the two twiddle tables.
-StaticLayout static_layout(int64_t n, int64_t L, bool mixed) {
-  const int64_t kp = L / 2 + 1;
+StaticLayout static_layout(int64_t n, bool mixed) {
+  const int64_t L = reserved_length_for(n), kp = L / 2 + 1;
   StaticLayout s{};
   s.arena = 0;
   s.kh = align_up(std::max<int64_t>(n * n * L + n * L * L, kp * kp * kp) * 16);
@@ -2040,7 +2084,7 @@ ori_status ori_green_noalloc(const ori_grid* g, double k, int32_t precision, con
   if (!(k > 0.0) || !std::isfinite(k)) return set_err(nullptr, ORI_ERR_INVALID_ARG, "k must be finite and > 0");
   if (precision != ORI_FP64 && precision != ORI_MIXED) return set_err(nullptr, ORI_ERR_INVALID_ARG, "bad precision");
   const bool mixed = precision == ORI_MIXED;
-  const StaticLayout sl = static_layout(g->n, L, mixed);
+  const StaticLayout sl = static_layout(g->n, mixed);
   if (sl.total > kStaticBytes)
     return set_err(nullptr, ORI_ERR_UNSUPPORTED,
                    "n = %lld needs %lld bytes of workspace; the static workspace holds %lld (n <= 64)",
@@ -2097,12 +2141,12 @@ ori_status ori_set_layout(ori_ctx c, int32_t precision, const ori_layout* in) {
   if (!in) return set_err(c, ORI_ERR_INVALID_ARG, "layout is NULL");
   if (precision != ORI_FP64 && precision != ORI_MIXED) return set_err(c, ORI_ERR_INVALID_ARG, "bad precision");
   const Knobs k{in->blk_lg, in->narrow, in->prefetch, in->znarrow, in->zplan};
-  if (!valid_knobs(c->n, c->L, k))
+  if (!valid_knobs(c->n, k))
     return set_err(c, ORI_ERR_INVALID_ARG,
                    "layout {blk_lg %d, narrow %d, prefetch %d, znarrow %d, zplan %d} is not valid for n = %lld "
                    "(padded length %lld%s)",
                    in->blk_lg, in->narrow, in->prefetch, in->znarrow, in->zplan, (long long)c->n, (long long)c->L,
-                   has_plan_variant(static_cast<int>(c->L)) ? "" : ", one radix plan");
+                   has_plan_variant(static_cast<int>(reserved_length_for(c->n))) ? "" : ", one radix plan");
   ORI_HIP(c, hipStreamSynchronize(c->stream));
   ORI_TRY(drop_graphs(c));
   c->knob[precision == ORI_MIXED ? 1 : 0] = k;
@@ -2145,7 +2189,7 @@ ori_status ori_tune(ori_ctx c, int32_t reps, ori_layout* best, double* ms_per_pr
           for (int znp = 0; znp <= 1 && st == ORI_OK; ++znp)
             for (int zp = 0; zp <= 1 && st == ORI_OK; ++zp) {
             const Knobs k{lg, np, pf, znp, zp};
-            if (!valid_knobs(c->n, c->L, k)) continue;
+            if (!valid_knobs(c->n, k)) continue;
             c->knob[f] = k;
             auto product = [&] {
               return matvec(c, fp, fp, plain_f1(x, S), epi(y, x, 1.0, nullptr, 0.0, S, 1.0, nullptr, 0), nullptr);

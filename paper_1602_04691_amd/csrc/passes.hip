@@ -48,13 +48,13 @@ __global__ void __launch_bounds__(BLOCK_C) k_contig_inv(ContigInvArgs a) {
 }
 
 template <typename T, int NP, bool INV, bool HIN, bool HOUT, bool EX>
-__global__ void __launch_bounds__(NP * TPP) k_strided(StridedArgs a) {
+__global__ void __launch_bounds__(block_np<NP>()) k_strided(StridedArgs a) {
   __shared__ __align__(16) unsigned char smem[strided_smem<T, NP>()];
   strided_body<T, NP, INV, HIN, HOUT, EX>(a, blockIdx.x, gridDim.x, smem);
 }
 
 template <typename T, int NP, bool PF, bool EX, bool SOFF, int PV>
-__global__ void __launch_bounds__(NP * z_tpp<T>(), (z_min_waves<T, NP, PF, PV, SOFF>())) k_zpass(ZArgs a) {
+__global__ void __launch_bounds__(block_np<NP>(z_tpp<T, PV>()), (z_min_waves<T, NP, PF, PV, SOFF>())) k_zpass(ZArgs a) {
   __shared__ __align__(16) unsigned char smem[z_smem<T, NP, PV>()];
   zpass_body<T, NP, PF, EX, SOFF, PV>(a, blockIdx.x, gridDim.x, smem);
 }
@@ -83,19 +83,19 @@ __device__ __forceinline__ cxd green_table(int m1, int m2, int m3, double k, dou
 // pass 1: pencils (m1, m2) in [0..n]^2 along the contiguous m3
 __global__ void __launch_bounds__(BLOCK_C) k_spectrum_first(SpectrumArgs a) {
   constexpr int n = L / 2, kp = n + 1;
-  __shared__ cxd lds[NPC * padded_row(L)];
-  using E = Engine<double, L, false>;
-  const int tid = threadIdx.x;
-  const int bt = tid % TPP, t = tid / TPP;
+  __shared__ cxd lds[NPC * contig_row()];
+  using E = Engine<double, L, false, TPP, 0, 0, IDLE_C>;
+  int t, bt;
+  contig_lane(threadIdx.x, t, bt);
   const int64_t pid = static_cast<int64_t>(blockIdx.x) * NPC + t;
-  const bool act = pid < static_cast<int64_t>(kp) * kp;  // one pencil per (m1, m2)
+  const bool act = pid < static_cast<int64_t>(kp) * kp && (!IDLE_C || bt < L);  // one pencil per (m1, m2)
   const int m1 = act ? static_cast<int>(pid / kp) : 0;
   const int m2 = act ? static_cast<int>(pid % kp) : 0;
   cxd* __restrict__ kh = static_cast<cxd*>(a.kh);
   auto load = [&](int e) -> cxd { return act ? green_table(m1, m2, e, a.k, a.spacing, static_cast<int>(a.n)) : cxd{}; };
   typename E::template RegsOf<0> g;
   E::template load_first<false>(g, bt, load);
-  LdsPencil<double> lp{lds + t * padded_row(L), 0};
+  LdsPencil<double> lp{lds + t * contig_row(), 1, contig_pad<false>()};
   E::template run<false>(g, bt, lp, static_cast<const cxd*>(a.tw), [&](auto& gl) {
     E::template store_last<KEEP_HALF1>(gl, bt, [&](int e, cxd v) {
       if (act) kh[pid * kp + e] = v;
@@ -104,14 +104,15 @@ __global__ void __launch_bounds__(BLOCK_C) k_spectrum_first(SpectrumArgs a) {
 }
 
 // passes 2 and 3: pencils (o, c) in [0..n]^2 along m2 (pass 2) or m1 (pass 3)
-__global__ void __launch_bounds__(block_s<double>()) k_spectrum_strided(SpectrumArgs a) {
+__global__ void __launch_bounds__(block_np<nps<double>()>()) k_spectrum_strided(SpectrumArgs a) {
   constexpr int n = L / 2, kp = n + 1;
   constexpr int NP = nps<double>();
   constexpr int64_t CT = (kp + NP - 1) / NP;
   __shared__ cxd lds[NP * L];
-  using E = Engine<double, L, false>;
+  using E = Engine<double, L, false, TPP, 0, 0, idle_np<NP>()>;
   const int tid = threadIdx.x;
-  const int t = tid % NP, bt = tid / NP;
+  const int t = tid % NP;
+  const int bt = idle_np<NP>() && tid >= NP * TPP ? L : tid / NP;
   // neighbouring column tiles share cache lines (rows of kp = n + 1 values
   // are not line aligned), so they run on one XCD
   const int64_t w = xcd_order(blockIdx.x, gridDim.x);
@@ -130,7 +131,7 @@ __global__ void __launch_bounds__(block_s<double>()) k_spectrum_strided(Spectrum
   };
   typename E::template RegsOf<0> g;
   E::template load_first<false>(g, bt, load);
-  LdsPencil<double> lp{lds + t, NP};
+  LdsPencil<double> lp{lds + t, NP, 0};
   E::template run<false>(g, bt, lp, static_cast<const cxd*>(a.tw), [&](auto& gl) {
     E::template store_last<KEEP_HALF1>(gl, bt, [&](int e, cxd v) {
       if (!act) return;
@@ -207,7 +208,7 @@ hipError_t contig_inv(int vp, int fp, const ContigInvArgs& a, hipStream_t st) {
 template <typename T, int NP>
 hipError_t strided_t(const StridedArgs& a, hipStream_t st) {
   hipError_t e = hipSuccess;
-  const dim3 grid(static_cast<unsigned>(a.n_outer * ((a.C + NP - 1) / NP))), block(NP * TPP);
+  const dim3 grid(static_cast<unsigned>(a.n_outer * ((a.C + NP - 1) / NP))), block(block_np<NP>());
   if (a.nv < 1 || 2 * a.nv - 1 > L) return hipErrorInvalidValue;
   const bool ex = 2 * a.nv == L;
   if (!a.inverse && a.half_in && !a.half_out)
@@ -235,32 +236,36 @@ int64_t zpass_blocks(int fprec, int np_sel) {
 }
 
 template <typename T, int NP, bool SOFF, int PV>
-hipError_t zpass_s(const ZArgs& a, const dim3& grid, const dim3& block, hipStream_t st) {
+hipError_t zpass_s(const ZArgs& a, const dim3& grid, hipStream_t st) {
+  const dim3 block(block_np<NP>(z_tpp<T, PV>()));
   const bool ex = 2 * a.n == L;
-  if (a.prefetch)
-    return ex ? launch_kernel((k_zpass<T, NP, true, true, SOFF, PV>), grid, block, st, a)
-              : launch_kernel((k_zpass<T, NP, true, false, SOFF, PV>), grid, block, st, a);
+  // the prefetch variant changes no bit and measured no faster, so only the
+  // lengths of the reserved set build it
+  if constexpr (reserved_length(L)) {
+    if (a.prefetch)
+      return ex ? launch_kernel((k_zpass<T, NP, true, true, SOFF, PV>), grid, block, st, a)
+                : launch_kernel((k_zpass<T, NP, true, false, SOFF, PV>), grid, block, st, a);
+  }
   return ex ? launch_kernel((k_zpass<T, NP, false, true, SOFF, PV>), grid, block, st, a)
             : launch_kernel((k_zpass<T, NP, false, false, SOFF, PV>), grid, block, st, a);
 }
 
 template <typename T, int NP, int PV>
-hipError_t zpass_p(const ZArgs& a, const dim3& grid, const dim3& block, hipStream_t st) {
-  if constexpr (L <= 512) {
-    if (a.e_lg <= z_align_lg<T, PV>()) return zpass_s<T, NP, true, PV>(a, grid, block, st);
-  }
-  return zpass_s<T, NP, false, PV>(a, grid, block, st);
+hipError_t zpass_p(const ZArgs& a, const dim3& grid, hipStream_t st) {
+  if (a.e_lg <= z_align_lg<T, PV>()) return zpass_s<T, NP, true, PV>(a, grid, st);
+  return zpass_s<T, NP, false, PV>(a, grid, st);
 }
 
 template <typename T, int NP>
 hipError_t zpass_t(const ZArgs& a, hipStream_t st) {
   if (a.rhs_slices < 1 || a.rhs_slices > a.nrhs) return hipErrorInvalidValue;
-  if (a.plan != 0 && (a.plan != 1 || !has_plan_variant(L))) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>((L / 2 + 1) * ((L + NP - 1) / NP) * a.rhs_slices)), block(NP * z_tpp<T>());
+  // a length without an alternative runs its one plan for either value
+  if (a.plan != 0 && a.plan != 1) return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>((L / 2 + 1) * ((L + NP - 1) / NP) * a.rhs_slices));
   if constexpr (has_plan_variant(L)) {
-    if (a.plan == 1) return zpass_p<T, NP, 1>(a, grid, block, st);
+    if (a.plan == 1) return zpass_p<T, NP, 1>(a, grid, st);
   }
-  return zpass_p<T, NP, 0>(a, grid, block, st);
+  return zpass_p<T, NP, 0>(a, grid, st);
 }
 
 hipError_t spectrum(const SpectrumArgs& a, hipStream_t st) {
@@ -273,12 +278,14 @@ hipError_t spectrum(const SpectrumArgs& a, hipStream_t st) {
   } else if (a.pass == 2 || a.pass == 3) {
     const int64_t np = nps<double>();
     const dim3 grid(static_cast<unsigned>(kp * ((kp + np - 1) / np)));
-    e = launch_kernel(k_spectrum_strided, grid, dim3(block_s<double>()), st, a);
+    e = launch_kernel(k_spectrum_strided, grid, dim3(block_np<nps<double>()>()), st, a);
   } else {
     return hipErrorInvalidValue;
   }
   return e;
 }
+
+int z_align(int fp) { return fp == PREC_F64 ? z_align_lg<double, 0>() : z_align_lg<float, 0>(); }
 
 hipError_t zpass(int fp, const ZArgs& a, hipStream_t st) {
   if (a.n < 1 || 2 * a.n - 1 > L || a.kp != L / 2 + 1) return hipErrorInvalidValue;
@@ -293,7 +300,7 @@ hipError_t zpass(int fp, const ZArgs& a, hipStream_t st) {
 
 const LengthKernels* ORI_CAT(kernels_L, ORI_L)() {
   static const LengthKernels k = {L, contig_fwd, contig_inv, strided, zpass, contig_blocks_per_rhs, strided_blocks,
-                                  zpass_blocks, spectrum};
+                                  zpass_blocks, spectrum, z_align};
   return &k;
 }
 

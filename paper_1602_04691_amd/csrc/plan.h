@@ -9,8 +9,28 @@ namespace ori {
 
 // Every supported padded length, one translation unit of FFT kernels each.
 #define ORI_FOR_EACH_L(X) \
+  X(2) X(4) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(72) X(80) X(96) \
+  X(100) X(108) X(128) X(144) X(160) X(192) X(200) X(216) X(256) X(288) X(320) X(360) \
+  X(384) X(400) X(432) X(512) X(576) X(640) X(720) X(768) X(1024)
+
+// The lengths whose work arrays a context reserves: the shortest of these
+// with L >= 2n - 1 sizes its workspace, so that ori_workspace_bytes, which
+// callers budget with, does not depend on the plan the passes run.  These
+// lengths also have the Z pass's prefetch variant.
+#define ORI_FOR_EACH_RESERVED_L(X) \
   X(2) X(4) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96) \
   X(128) X(192) X(256) X(384) X(512) X(1024)
+
+constexpr bool reserved_length(int L) {
+  switch (L) {
+#define ORI_RESERVED(Lv) case Lv:
+    ORI_FOR_EACH_RESERVED_L(ORI_RESERVED)
+#undef ORI_RESERVED
+    return true;
+    default:
+      return false;
+  }
+}
 
 struct RadixPlan {
   int n;     // number of Stockham stages
@@ -23,6 +43,14 @@ struct RadixPlan {
 // and twiddles of the fused Z pass at 4 waves per SIMD, where radix 16 needs
 // over 200 VGPRs.  L = 16 is 4 x 4 (four threads per pencil), so that its
 // pass bodies fit the register budget of the multi-problem launches.
+//
+// The lengths between the powers of two (72, 100, 108, 144, ... 768)
+// keep an n whose 2n is not planned from paying for the next power of two
+// (n = 300 on L = 640 instead of 1024 transforms 2.6 times fewer points).
+// They use radices 6, 9, 10 and 12 to stay at two or three stages; the first
+// radix is even, and the last is 8 or smaller where the length allows it,
+// because the spectrum of the fused Z pass is held in registers in the shape
+// of the last stage.
 constexpr RadixPlan radix_plan(int L) {
   switch (L) {
     case 2: return {1, {2, 0, 0, 0}};
@@ -38,13 +66,29 @@ constexpr RadixPlan radix_plan(int L) {
     case 40: return {2, {8, 5, 0, 0}};
     case 48: return {3, {8, 2, 3, 0}};
     case 64: return {2, {8, 8, 0, 0}};
+    case 72: return {2, {8, 9, 0, 0}};
     case 80: return {3, {8, 2, 5, 0}};
     case 96: return {3, {8, 4, 3, 0}};
+    case 100: return {2, {10, 10, 0, 0}};
+    case 108: return {2, {12, 9, 0, 0}};
     case 128: return {3, {8, 4, 4, 0}};
+    case 144: return {2, {12, 12, 0, 0}};
+    case 160: return {3, {4, 10, 4, 0}};
     case 192: return {3, {8, 8, 3, 0}};
+    case 200: return {3, {10, 2, 10, 0}};
+    case 216: return {3, {6, 6, 6, 0}};
     case 256: return {3, {8, 8, 4, 0}};
-    case 384: return {4, {8, 4, 4, 3}};
+    case 288: return {3, {6, 8, 6, 0}};
+    case 320: return {3, {8, 5, 8, 0}};
+    case 360: return {3, {6, 10, 6, 0}};
+    case 384: return {3, {8, 6, 8, 0}};
+    case 400: return {3, {10, 4, 10, 0}};
+    case 432: return {3, {8, 9, 6, 0}};
     case 512: return {3, {8, 8, 8, 0}};
+    case 576: return {3, {8, 9, 8, 0}};
+    case 640: return {3, {8, 10, 8, 0}};
+    case 720: return {3, {10, 9, 8, 0}};
+    case 768: return {3, {8, 12, 8, 0}};
     case 1024: return {4, {8, 8, 4, 4}};
     default: return {0, {0, 0, 0, 0}};
   }
@@ -56,7 +100,8 @@ constexpr RadixPlan radix_plan(int L) {
 // that the Z workgroup shape is unchanged; the first radix stays even.  At
 // L = 1024 variant 1 is 16 x 8 x 8: two exchanges per transform instead of
 // three with the same 64 threads per pencil (complex128 Z 6.04 vs 6.52 ms
-// at n = 512, its default there).  Lengths without an alternative (L = 64
+// at n = 512, its default there; 8 x 16 x 8 on 128 threads, whose 122
+// registers allow twice the wavefronts, takes 6.60 ms).  Lengths without an alternative (L = 64
 // and most short ones) have variant 1 equal to the default.
 constexpr RadixPlan radix_plan(int L, int variant) {
   if (variant == 1) switch (L) {
@@ -87,18 +132,34 @@ constexpr bool has_plan_variant(int L) { return !same_plan(radix_plan(L, 1), rad
 
 constexpr bool supported_length(int L) { return radix_plan(L).n > 0; }
 
+// Butterflies of one pencil in the stage with the fewest and the most.
+constexpr int fewest_butterflies(int L, const RadixPlan& p) {
+  int t = L;
+  for (int s = 0; s < p.n; ++s)
+    if (L / p.r[s] < t) t = L / p.r[s];
+  return t;
+}
+constexpr int most_butterflies(int L, const RadixPlan& p) {
+  int t = 0;
+  for (int s = 0; s < p.n; ++s)
+    if (L / p.r[s] > t) t = L / p.r[s];
+  return t;
+}
+
 // Threads per pencil: the smallest butterfly count over the stages, so that
 // no stage leaves threads idle in its widest configuration, capped at two
 // wavefronts (L = 1024: one radix-8 butterfly per thread keeps a complex128
-// thread within 128 registers).
+// thread within 128 registers).  The lengths between the reserved ones take
+// the largest count where the counts lie close together (L = 640: 80, 64,
+// 80): one butterfly per thread and stage holds half the registers of a
+// second, mostly empty round, and the threads without a butterfly are whole
+// wavefronts of the strided passes, which skip the stage.
 constexpr int threads_per_pencil(int L, int variant = 0) {
-  RadixPlan p = radix_plan(L, variant);
-  int t = L;
-  for (int s = 0; s < p.n; ++s) {
-    int b = L / p.r[s];
-    if (b < t) t = b;
-  }
-  return t > 128 ? 128 : t;
+  const RadixPlan p = radix_plan(L, variant);
+  if (L == 160) return 20;  // 40, 16, 40
+  const int lo = fewest_butterflies(L, p), hi = most_butterflies(L, p);
+  if (!reserved_length(L) && hi <= 2 * lo && hi != 64) return hi;
+  return lo > 128 ? 128 : lo;
 }
 
 constexpr int pow2_floor(int x) {
@@ -112,9 +173,13 @@ constexpr int pow2_floor(int x) {
 // complex128, 16 x 8 B for complex64); contiguous passes only need enough
 // threads to fill the workgroup.
 // Workgroups are whole wavefronts (64 lanes): the reductions use full-wave
-// shuffles.
+// shuffles.  block_threads rounds NP pencils up to whole wavefronts; the
+// lanes beyond NP * TPP own no butterfly (Engine's IDLE).  More pencils are
+// taken while more than an eighth of the lanes would idle.
+constexpr int block_threads(int threads) { return (threads + 63) / 64 * 64; }
 constexpr int whole_waves(int np, int tpp) {
-  while ((np * tpp) % 64 != 0) np *= 2;
+  while ((block_threads(np * tpp) - np * tpp) * 8 > block_threads(np * tpp) && block_threads(2 * np * tpp) <= 1024)
+    np *= 2;
   return np;
 }
 
@@ -128,11 +193,22 @@ constexpr int pencils_strided(int L, int elem_bytes) {
   return whole_waves(np, tpp);
 }
 
+// LDS slots of one padded contiguous pencil row
+constexpr int padded_row(int L) { return L + L / 8; }
+
+// Contiguous passes of the lengths between the reserved ones take fewer
+// pencils and up to a fifth of idle lanes: their rows need no neighbours, and
+// half the LDS per workgroup (25 instead of 51 KB at L = 400) keeps twice the
+// workgroups resident.
 constexpr int pencils_contig(int L) {
   int tpp = threads_per_pencil(L);
   int np = pow2_floor(256 / tpp);
   if (np < 1) np = 1;
-  return whole_waves(np, tpp);
+  if (reserved_length(L) || (block_threads(np * tpp) - np * tpp) * 5 > block_threads(np * tpp))
+    np = whole_waves(np, tpp);
+  // complex128 rows within the 64 KB of dynamic LDS of a multi-problem launch
+  while (L <= 256 && np * padded_row(L) * 16 > 64 * 1024) np /= 2;
+  return np;
 }
 
 }  // namespace ori
