@@ -395,7 +395,7 @@ def next_workload(a):
         # counts (committed summary on the current sources) as context
         flops = value / 2 * (FIELD_FLOPS["field"] + FIELD_FLOPS["far"])  # M points + M directions
         ipp = read_profile_value(f"field_n{n}_valu.txt", "valu_insts_per_pair")
-        roofline = {"bound": "alu", "kernel": "k_field_partial", "achieved": round(flops / 1e12, 4),
+        roofline = {"bound": "alu", "kernel": "k_field_near", "achieved": round(flops / 1e12, 4),
                     "peak": FP64_VECTOR_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(flops / 1e12 / FP64_VECTOR_TFLOPS, 4), "traffic": None,
                     "flops_per_pair": FIELD_FLOPS, "valu_insts_per_pair": ipp,

@@ -254,19 +254,24 @@ hipError_t launch_gather_scalars(const MultiFin* tab, int32_t np, ScalarBlock* o
 // (red_blocks(P), nrhs) workgroups; right-hand side rhs writes partials
 // [rhs * red_blocks(P), (rhs + 1) * red_blocks(P)).
 // ---------------------------------------------------------------------------
-// Field sums over the cells (eq. 2.10): points a.pts[m0 .. m0 + mb) of M,
-// cells in chunks of `chunk`, partials [nrhs][mb][nchunk], results
-// out[nrhs][M].
+// Field sums over the cells (eq. 2.10): points a.pts[m0 .. m0 + mb) of M.
+// The columns (i2, i3) of cells are split in blocks of field_columns(far) and
+// their i1 in nch ranges: partials [nrhs][mb][nparts], nparts = blocks * nch;
+// results out[nrhs][M].
 struct FieldArgs {
   const cxd* u;      // [nrhs][P] solution of eq. 2.19
   const cxd* D;      // [P]
   const double* pts; // [M][3] points (field) or unit directions (far field)
   cxd* part;
   cxd* out;
-  int64_t n, P, M, m0, mb, nchunk, chunk, nrhs;
+  int64_t n, P, M, m0, mb, nparts, nrhs;
+  int32_t nch, pad;
   double dn, side, offset, k;
+  double kt_hi, kt_lo;  // k in 256ths of a turn, k 256 / (2 pi), as an unevaluated sum
   double origin[3];
+  double corner[6];  // the cube around the cell points: lower, then upper corner
 };
+int64_t field_columns(bool far);
 hipError_t launch_field(const FieldArgs& a, bool far, hipStream_t st);
 // q = -D u over the batch
 hipError_t launch_charges(const void* D, const void* u, int64_t P, int64_t nrhs, void* q, hipStream_t st);

@@ -1601,21 +1601,35 @@ ori_status field_sum(ori_ctx c, const void* u, const double* pts, int64_t M, voi
   a.P = c->P;
   a.M = M;
   a.nrhs = c->nrhs;
-  a.chunk = int64_t{1} << 16;
-  a.nchunk = (c->P + a.chunk - 1) / a.chunk;
   a.dn = static_cast<double>(c->n);
   a.side = c->grid.side;
   a.offset = c->grid.cell_offset;
   a.k = c->k;
-  for (int d = 0; d < 3; ++d) a.origin[d] = c->grid.origin[d];
-  // points per launch: the partials [nrhs][mb][nchunk] fit the P-value scratch
-  int64_t mb = c->P / (c->nrhs * a.nchunk);
+  const long double kt = static_cast<long double>(c->k) * 40.743665431525205956834243423364L;  // 256 / (2 pi)
+  a.kt_hi = static_cast<double>(kt);
+  a.kt_lo = static_cast<double>(kt - static_cast<long double>(a.kt_hi));
+  for (int d = 0; d < 3; ++d) {
+    a.origin[d] = c->grid.origin[d];
+    a.corner[d] = a.origin[d] + a.side * a.offset / a.dn;
+    a.corner[3 + d] = a.origin[d] + a.side * (a.dn - 1.0 + a.offset) / a.dn;
+  }
+  // Parts: the blocks of columns; their i1 split further (to 8 at least)
+  // while the launch has fewer than 2048 workgroups of 4 points, and the
+  // partials [nrhs][points][parts] fit the P-value scratch.
+  const int64_t cblocks = (c->n * c->n + field_columns(far) - 1) / field_columns(far);
+  const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(M, 16384) / 4) * c->nrhs;
+  int64_t nch = std::min<int64_t>((2048 + cblocks * groups - 1) / (cblocks * groups), (c->n + 7) / 8);
+  nch = std::max<int64_t>(1, std::min(nch, c->P / (c->nrhs * cblocks)));
+  a.nch = static_cast<int32_t>(nch);
+  a.nparts = cblocks * nch;
+  // points per launch
+  int64_t mb = c->P / (c->nrhs * a.nparts);
   if (mb < 1) mb = 1;
   if (mb > 65535) mb = 65535;
   for (int64_t m0 = 0; m0 < M; m0 += mb) {
     a.m0 = m0;
     a.mb = std::min(mb, M - m0);
-    if (c->nrhs * a.mb * a.nchunk > c->P) return set_err(c, ORI_ERR_UNSUPPORTED, "field scratch too small");
+    if (c->nrhs * a.mb * a.nparts > c->P) return set_err(c, ORI_ERR_UNSUPPORTED, "field scratch too small");
     ORI_TRY(launch(c, K_ELEMWISE, PREC_F64, [&] { return launch_field(a, far, c->stream); }));
   }
   ORI_HIP(c, hipStreamSynchronize(c->stream));

@@ -1,0 +1,106 @@
+"""The field and far-field sums against direct sums in torch (64 bits): few
+and many points (1 and 4 points per thread), a last group that is not full,
+grids with idle columns, several parts per point, several right-hand sides,
+points on cells, points so far away that the phase needs the library's
+argument reduction, and points that are not finite."""
+import math
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1602_04691_amd as ori  # noqa: E402
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def cells(n, side, origin, off):
+    # on the host: torch divides a GPU tensor by a number through its rounded
+    # reciprocal, and a point must equal its cell's coordinates exactly
+    t = [(origin[d] + side * (torch.arange(n, dtype=torch.float64) + off) / n).cuda() for d in range(3)]
+    return torch.stack(torch.meshgrid(*t, indexing="ij"), dim=-1).reshape(-1, 3)
+
+
+def direct(k, X, q, pts, far):
+    out = []
+    for m in range(pts.shape[0]):
+        if far:
+            ph = -k * (X * pts[m]).sum(dim=1)
+            g = torch.polar(torch.full_like(ph, 1 / (4 * math.pi)), ph)
+        else:
+            r = (X - pts[m]).norm(dim=1)
+            ok = r > 0
+            g = torch.where(ok, torch.polar(1 / (4 * math.pi * torch.where(ok, r, 1.0)), k * r), 0)
+        out.append((g * q).sum(dim=1))
+    return torch.stack(out, dim=1).reshape(-1)  # [nrhs][M]
+
+
+@pytest.mark.parametrize("n,M,R", [(1, 3, 1), (5, 1, 2), (17, 6, 1), (33, 5, 2), (40, 1030, 1), (64, 9, 3), (260, 2, 1)])
+def test_sums_against_direct(n, M, R):
+    k, side, origin, off = 4.7, 1.3, (0.2, -0.1, 0.05), 0.5
+    say(f"[field] n={n} M={M} nrhs={R}")
+    g = torch.Generator(device="cuda").manual_seed(n * 1000 + M)
+    P = n ** 3
+    rnd = lambda *s: torch.randn(*s, dtype=torch.float64, device="cuda", generator=g)
+    h = torch.complex(-1 + 0.1 * rnd(P), 0.5 + 0.1 * rnd(P))
+    u = torch.complex(rnd(R * P), rnd(R * P))
+    d = rnd(M, 3)
+    beta = (d / d.norm(dim=1, keepdim=True)).contiguous()
+    X = cells(n, side, origin, off)
+    pts = torch.tensor([0.5, 0.4, 0.6], dtype=torch.float64, device="cuda") + 2.0 * beta * (1 + rnd(M, 1).abs())
+    pts[M // 2] = X[P // 2]  # a cell point: left out of its own sum
+    with ori.ori_create(n, side=side, origin=origin, cell_offset=off, nrhs=R) as ctx:
+        ori.ori_load(ctx, k, h, None, u)
+        q = ori.ori_charges(ctx, u).view(R, P)
+        for far, x in ((False, pts.contiguous()), (True, beta)):
+            got = (ori.ori_far_field if far else ori.ori_scattered_field)(ctx, u, x)
+            ref = direct(k, X, q, x, far)
+            # random charges: the sum is about sqrt(P) terms, each good to a
+            # few ulps of its phase (k r <= 40)
+            e = ((got - ref).abs().max() / ref.abs().max()).item()
+            say(f"   far={far}: {e:.2e}")
+            assert e <= 1e-13
+        assert ori.ori_check_guards(ctx) == 0
+
+
+def test_phase_no_worse_than_the_library_at_any_distance():
+    # one cell: v = q e^{ikr} / (4 pi r) at r from 1e-3 to 1e17 (the last ones
+    # beyond the table's range), against r and the phase in extended precision
+    import numpy as np
+    k = 3.7
+    say("[field] one cell, r up to 1e17")
+    r = np.concatenate([np.geomspace(1e-3, 1e6, 400), np.geomspace(1e7, 1e13, 13), [1e15, 1e16, 1e17]])
+    x = torch.zeros(len(r), 3, dtype=torch.float64)
+    x[:, 0] = torch.from_numpy(r)
+    one = torch.ones(1, dtype=torch.complex128, device="cuda")
+    with ori.ori_create(1, cell_offset=0.0) as ctx:
+        ori.ori_load(ctx, k, one, None, one)
+        v = ori.ori_scattered_field(ctx, one, x.cuda()).cpu().numpy()
+    rl = r.astype(np.longdouble)
+    th = np.fmod(np.longdouble(k) * rl, 2 * np.longdouble("3.14159265358979323846264338327950288"))
+    ref = -4 * math.pi * np.exp(1j * th.astype(np.clongdouble)) / (4 * np.longdouble(math.pi) * rl)
+    err = np.abs(v - ref) / np.abs(ref)
+    # 1/r to an ulp, and a phase error of an ulp of k r
+    bar = 4 * 2.3e-16 * (1 + k * r)
+    assert np.all((err <= bar) | (k * r > 1e12)), (err / bar).max()
+    assert np.all(np.isfinite(v)) and np.allclose(np.abs(v), 1 / r, rtol=1e-14)
+
+
+def test_points_that_are_not_finite():
+    # as ever: a NaN point has no cell at a positive distance, an infinite one
+    # a phase that is not a number
+    n, k = 6, 2.0
+    say("[field] NaN and infinite points")
+    one = torch.ones(n ** 3, dtype=torch.complex128, device="cuda")
+    x = torch.full((6, 3), 2.0, dtype=torch.float64, device="cuda")
+    x[1, 2] = float("nan")
+    x[4, 0] = float("inf")
+    with ori.ori_create(n) as ctx:
+        ori.ori_load(ctx, k, one, None, one)
+        v = ori.ori_scattered_field(ctx, one, x).cpu()
+    assert v[1] == 0 and torch.isnan(v[4].real) and torch.isfinite(torch.view_as_real(v[[0, 2, 3, 5]])).all()
+    assert torch.allclose(v[[0, 2, 3, 5]], v[0].expand(4), rtol=1e-14, atol=0)
