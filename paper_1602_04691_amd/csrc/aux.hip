@@ -249,13 +249,14 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       break;
     }
     case FIN_MU: {
+      if (sc->flags & FLAG_DONE) break;  // frozen: alpha stays for k_x_flush
       sc->mu_re = s0;
       sc->mu_im = s1;
       sc->pp = s3;
       sc->qq = s2;
       const double mag = hypot(s0, s1);
-      if (s3 == 0.0 || (sc->flags & FLAG_DONE)) {
-        sc->alpha_re = 0.0;  // converged, r = p = 0, or broken down: nothing moves
+      if (s3 == 0.0) {
+        sc->alpha_re = 0.0;  // r = p = 0: nothing moves
         sc->alpha_im = 0.0;
       } else if (mag <= eps * sqrt(s2 * s3)) {
         sc->flags |= FLAG_BREAKDOWN_MU;
@@ -315,6 +316,7 @@ __device__ __forceinline__ void update_body(cx<V>* __restrict__ x, const cx<V>* 
                                             const ScalarBlock* __restrict__ scb, double* __restrict__ partials,
                                             int64_t bid, int64_t nb, int64_t rhs) {
   const ScalarBlock* sc = scb + rhs;
+  if (sc->flags & FLAG_DONE) return;  // frozen: FIN_RHO reads no partials either
   const int64_t off = rhs * P;
   const cxd al = {sc->alpha_re, sc->alpha_im};
   const bool moving = al.re != 0.0 || al.im != 0.0;

@@ -40,8 +40,13 @@ enum : int32_t {
   FLAG_ZERO_RESIDUAL = 4,  // r == 0 exactly
   FLAG_BAD_INPUT = 8,      // NaN / Inf in a right-hand side u0, met in ori_load
   FLAG_BAD_COEFF = 32,     // NaN / Inf in h or N, or N < 0, met in ori_load (sc[0])
-  FLAG_CONVERGED = 16,     // rr <= rr_target: alpha = 0 from now on
+  FLAG_CONVERGED = 16,     // rr <= rr_target
 };
+// A right-hand side with one of these flags is frozen: every kernel of a COCG
+// iteration skips it, so an iteration launched after the last one needed
+// (the host reads the flags one block of iterations late) changes nothing.
+// alpha keeps the value of its last iteration for the step x += alpha p that
+// is still pending (k_x_flush).
 constexpr int32_t FLAG_DONE = FLAG_BREAKDOWN_RHO | FLAG_BREAKDOWN_MU | FLAG_ZERO_RESIDUAL | FLAG_CONVERGED;
 
 enum Prec : int { PREC_F64 = 0, PREC_F32 = 1 };
@@ -58,7 +63,7 @@ struct ContigFwdArgs {
   void* xvec;           // COCG iterate (V): x += alpha p with the alpha and p of the
                         // previous iteration, before p is replaced (NULL: no update)
   const void* s_in;     // diagonal scale (V) or NULL
-  const ScalarBlock* sc;  // [nrhs]
+  const ScalarBlock* sc;  // [nrhs]; COCG: a right-hand side that is done is skipped
   int32_t mode;         // 0 PLAIN, 1 COCG
   int32_t first;        // COCG: first iteration
   int32_t half_in;      // 1: only the first L/2 entries of each pencil are input (zero padding)
@@ -86,6 +91,7 @@ struct ContigInvArgs {
   int32_t pad;
   int64_t nrhs, ppr, in_pitch, out_pitch;
   const void* tw;
+  const ScalarBlock* sc;  // [nrhs]: a right-hand side that is done (FLAG_DONE) is skipped; NULL: none
 };
 
 // F2 / I2: DFT along a strided axis.  Pencil (o, c) element e lives at
@@ -103,6 +109,7 @@ struct StridedArgs {
   int64_t out_hi, out_lo, out_axis;
   int32_t inverse, half_in, half_out, np_sel;  // np_sel: 0 wide tiles, 1 narrow tiles
   const void* tw;
+  const ScalarBlock* sc;  // as ContigInvArgs; right-hand side o / nv
 };
 
 // Z: forward DFT along i1 (first n inputs), multiply by the kernel spectrum,
@@ -128,6 +135,7 @@ struct ZArgs {
   int64_t kp;
   const void* tw;
   int32_t plan;
+  const ScalarBlock* sc;  // as ContigInvArgs
 };
 
 // Kernel spectrum: passes 1 and 2 in place on an octant scratch
@@ -354,8 +362,8 @@ enum FinalizeMode : int32_t {
 hipError_t launch_finalize(const double* partials, int64_t nblk, int64_t nrhs, ScalarBlock* sc, int32_t mode,
                            double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, hipStream_t st);
 // r -= alpha q (and x += alpha p when x is not NULL); partials
-// {r^T r, ||r||^2} on (update_blocks(P, prec), nrhs) workgroups; converged
-// right-hand sides (alpha = 0) stay as they are
+// {r^T r, ||r||^2} on (update_blocks(P, prec), nrhs) workgroups; right-hand
+// sides that are done stay as they are
 hipError_t launch_update(int prec, void* x, const void* p, void* r, const void* q, int64_t P, int64_t nrhs,
                          const ScalarBlock* sc, double* partials, hipStream_t st);
 // x += alpha p per right-hand side (the update left pending by the last

@@ -259,12 +259,17 @@ struct IterGraph {
   };
   std::vector<Entry> entries;
   hipEvent_t done = nullptr;  // recorded after a replay, waited on by each member's stream
+  // recorded after the copies of the scalars of a block of iterations, for
+  // even and odd blocks (group_cocg)
+  hipEvent_t read[2] = {nullptr, nullptr};
   void release() {
     for (auto& e : entries)
       if (e.exec) (void)hipGraphExecDestroy(e.exec);
     entries.clear();
-    if (done) (void)hipEventDestroy(done);
-    done = nullptr;
+    for (hipEvent_t* e : {&done, &read[0], &read[1]}) {
+      if (*e) (void)hipEventDestroy(*e);
+      *e = nullptr;
+    }
   }
 };
 constexpr size_t kGraphCacheEntries = 8;
@@ -313,6 +318,7 @@ struct ori_ctx_s {
   double* partials = nullptr;
   ScalarBlock* sc = nullptr;       // [nrhs]
   ScalarBlock* sc_host = nullptr;  // pinned mirror
+  ScalarBlock* sc_ring = nullptr;  // pinned, [2][nrhs]: the scalars of the last two blocks of iterations
   double* outer_m = nullptr;       // [2 nrhs]: refinement multipliers, then inner tolerances^2
   double* outer_m_host = nullptr;  // pinned
   // every device workspace is carved from one block (device_pool), the two
@@ -598,7 +604,9 @@ ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, P
   const int lg = kn.blk_lg;
   const int64_t Bk = int64_t{1} << lg;
   const int ns = kn.np_sel;
-  out->f2 = StridedArgs{A, B, R * n, L, n, 0, lg, n * L, 0, L, L * L * Bk, L, Bk * L, 0, 1, 0, ns, tw};
+  // a COCG product skips the right-hand sides that are done
+  const ScalarBlock* sc = f1.mode == 1 ? f1.sc : nullptr;
+  out->f2 = StridedArgs{A, B, R * n, L, n, 0, lg, n * L, 0, L, L * L * Bk, L, Bk * L, 0, 1, 0, ns, tw, sc};
 
   // Small grids (a batch at small n) are split over the right-hand sides,
   // so that the pass has enough workgroups to fill the chip; no slice is
@@ -607,9 +615,9 @@ ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, P
   int64_t rs = std::min<int64_t>(R, (kZMinWorkgroups + zbase - 1) / zbase);
   if (rs > 1) rs = (R + (R + rs - 1) / rs - 1) / ((R + rs - 1) / rs);
   out->z = ZArgs{B,  n,  lg, kn.z_np, L * L * Bk, L, Bk * L, R, n * L * L, kn.zpf, static_cast<int32_t>(rs),
-                 kh, L / 2 + 1, tw, kn.zplan};
+                 kh, L / 2 + 1, tw, kn.zplan, sc};
 
-  out->i2 = StridedArgs{B, A, R * n, L, n, lg, 0, L * L * Bk, L, Bk * L, n * L, 0, L, 1, 0, 1, ns, tw};
+  out->i2 = StridedArgs{B, A, R * n, L, n, lg, 0, L * L * Bk, L, Bk * L, n * L, 0, L, 1, 0, 1, ns, tw, sc};
 
   i1.in = A;
   i1.nrhs = R;
@@ -617,6 +625,7 @@ ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, P
   i1.in_pitch = L;
   i1.out_pitch = n;
   i1.tw = tw;
+  i1.sc = sc;
   out->i1 = i1;
 
   const int64_t cb = c->K->contig_blocks_per_rhs(n * n);
@@ -819,7 +828,7 @@ struct MultiCache {
   std::vector<std::unique_ptr<MultiSet>> sets;
   IterGraph* graphs = nullptr;  // the group's graph caches, [2]
   int64_t iterations = 0;       // COCG iterations run this way (per member set, not per member)
-  ScalarBlock* gathered = nullptr;      // pinned, one block per member: the scalars after a block of iterations
+  ScalarBlock* gathered = nullptr;      // pinned, [2][member]: the scalars after even and odd blocks of iterations
   ScalarBlock* gathered_dev = nullptr;  // its device address
   void release() {
     if (graphs) {
@@ -943,29 +952,26 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
   return ORI_OK;
 }
 
-// The scalar blocks of every member of m on the host after work that ran
-// on the first member's stream: one gather into pinned memory, one wait,
-// then each member's mirror.
-ori_status multi_sync_scalars(MultiCache& mc, const MultiSet& m) {
+// The scalar blocks of every member of m gathered into pinned memory (slot 0
+// or 1) by a launch on the first member's stream.
+constexpr size_t kGatheredBytes = 2 * kGroupMaxProblems * sizeof(ScalarBlock);
+ori_status multi_gather_scalars(MultiCache& mc, const MultiSet& m, int slot) {
   ori_ctx c0 = m.members.front();
   const int32_t np = static_cast<int32_t>(m.members.size());
   if (np > kGroupMaxProblems) return set_err(c0, ORI_ERR_INVALID_ARG, "%d problems in one group", np);
   if (!mc.gathered) {
-    if (pool_host_malloc(kGroupMaxProblems * sizeof(ScalarBlock), reinterpret_cast<void**>(&mc.gathered)) !=
-        hipSuccess) {
+    if (pool_host_malloc(kGatheredBytes, reinterpret_cast<void**>(&mc.gathered)) != hipSuccess) {
       mc.gathered = nullptr;
       return set_err(c0, ORI_ERR_OUT_OF_MEMORY, "hipHostMalloc of the gathered scalars failed");
     }
     if (hipHostGetDevicePointer(reinterpret_cast<void**>(&mc.gathered_dev), mc.gathered, 0) != hipSuccess) {
-      host_pool().give(-1, kGroupMaxProblems * sizeof(ScalarBlock), mc.gathered);
+      host_pool().give(-1, kGatheredBytes, mc.gathered);
       mc.gathered = nullptr;
       mc.gathered_dev = nullptr;
       return set_err(c0, ORI_ERR_DEVICE, "hipHostGetDevicePointer of the gathered scalars failed");
     }
   }
-  ORI_HIP(c0, launch_gather_scalars(m.fin_mu, np, mc.gathered_dev, c0->stream));
-  ORI_HIP(c0, hipStreamSynchronize(c0->stream));
-  for (int32_t i = 0; i < np; ++i) m.members[i]->sc_host[0] = mc.gathered[i];
+  ORI_HIP(c0, launch_gather_scalars(m.fin_mu, np, mc.gathered_dev + slot * kGroupMaxProblems, c0->stream));
   return ORI_OK;
 }
 
@@ -1081,40 +1087,76 @@ ori_status sync_members(const Members& ms) {
 // replay of a graph over the members still running; a shorter block (an
 // iteration budget running out) runs eagerly.  Each member runs exactly the
 // kernels of its own solve, so results do not depend on the other members.
+//
+// The host reads the scalars of a block while the next one runs: block k + 1
+// is launched before the scalars of block k are waited for, so the GPU does
+// not idle through the round trip (about 15 us, a third of an iteration at n
+// = 32).  Members that block k finished are frozen on the device, and block
+// k + 1 skips them (FLAG_DONE), so the results are those of waiting every
+// time.  This holds where one stream runs the whole block: a single member,
+// or the launches that serve every member (multi_ok).
 ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budget, int check_every, bool use_graph,
                       IterGraph& cache, MultiCache* mc, std::vector<int>* ran) {
   ran->assign(ms.size(), 0);
   ORI_TRY(sync_members(ms));
+  bool ahead = true;
   for (ori_ctx c : ms) {
     trace_cocg(c, prec);
     use_graph = use_graph && !c->prof && !c->check_guards;
+    ahead = ahead && !c->prof && !c->check_guards && !c->trace;
   }
   std::vector<size_t> act;
   for (size_t i = 0; i < ms.size(); ++i)
     if (!all_done(ms[i]) && budget[i] > 0) act.push_back(i);
-  int it = 0;
-  while (!act.empty()) {
-    int blk = check_every;
-    for (size_t i : act) blk = std::min(blk, budget[i] - (*ran)[i]);
+
+  // one launched block of iterations: its members, its length, the launches
+  // that served it and where its scalars go
+  struct Block {
+    std::vector<size_t> act;
+    const MultiSet* mset = nullptr;
+    int blk = 0, slot = 0;
+    bool one_stream = false;
+  };
+  int it = 0, count = 0;
+  // launches the next block of the members act, `pending` iterations after
+  // the ones counted in ran
+  auto launch_block = [&](const std::vector<size_t>& who, int pending, Block* b) -> ori_status {
+    b->act = who;
+    b->slot = count++ & 1;
+    b->blk = check_every;
+    for (size_t i : who) b->blk = std::min(b->blk, budget[i] - (*ran)[i] - pending);
     Members active;
-    for (size_t i : act) active.push_back(ms[i]);
+    for (size_t i : who) active.push_back(ms[i]);
     // members that fit run in one launch per kernel (multi_ok)
     const MultiSet* mset = nullptr;
     if (mc && multi_ok(active, prec)) {
       if (mc->sets.size() >= kMultiSetsMax) mc->release();  // with every graph that points into them
       ORI_TRY(multi_set(*mc, active, prec, &mset));
     }
+    b->mset = mset;
+    b->one_stream = mset || active.size() == 1;
     hipGraphExec_t exec = nullptr;
-    if (use_graph && blk == check_every) ORI_TRY(iteration_graph(active, prec, blk, it == 0, mset, cache, &exec));
+    if (use_graph && b->blk == check_every)
+      ORI_TRY(iteration_graph(active, prec, b->blk, it == 0, mset, cache, &exec));
     ori_ctx c0 = active.front();
-    if (mset) mc->iterations += blk;
     if (exec) {
       ORI_HIP(c0, hipGraphLaunch(exec, c0->stream));
     } else if (mset) {
-      for (int j = 0; j < blk; ++j) ORI_TRY(multi_iteration(*mset, it + j == 0, c0->stream));
+      for (int j = 0; j < b->blk; ++j) ORI_TRY(multi_iteration(*mset, it + j == 0, c0->stream));
     } else {
-      for (int j = 0; j < blk; ++j)
+      for (int j = 0; j < b->blk; ++j)
         for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0));
+    }
+    // the scalars after the block
+    if (mset)
+      ORI_TRY(multi_gather_scalars(*mc, *mset, b->slot));
+    else if (b->one_stream)
+      ORI_HIP(c0, hipMemcpyAsync(c0->sc_ring + b->slot * c0->nrhs, c0->sc, c0->nrhs * sizeof(ScalarBlock),
+                                 hipMemcpyDeviceToHost, c0->stream));
+    if (b->one_stream) {
+      hipEvent_t& ev = cache.read[b->slot];
+      if (!ev) ORI_HIP(c0, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+      ORI_HIP(c0, hipEventRecord(ev, c0->stream));
     }
     if (exec || mset) {
       // a replay, or the multi-problem launches, ran every member's work on
@@ -1125,18 +1167,62 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
       for (ori_ctx c : active)
         if (c->stream != c0->stream) ORI_HIP(c, hipStreamWaitEvent(c->stream, cache.done, 0));
     }
-    it += blk;
-    for (size_t i : act) (*ran)[i] += blk;
-    if (mset)
-      ORI_TRY(multi_sync_scalars(*mc, *mset));  // the block ran on the first member's stream
-    else
-      ORI_TRY(sync_members(active));
-    std::vector<size_t> next;
-    for (size_t i : act) {
-      trace_cocg(ms[i], prec);
-      if (!all_done(ms[i]) && (*ran)[i] < budget[i]) next.push_back(i);
+    it += b->blk;
+    return ORI_OK;
+  };
+  // waits for the scalars of a block and brings them to the members' mirrors
+  auto read_block = [&](const Block& b) -> ori_status {
+    ori_ctx c0 = ms[b.act.front()];
+    if (!b.one_stream) {
+      Members active;
+      for (size_t i : b.act) active.push_back(ms[i]);
+      return sync_members(active);
     }
-    act.swap(next);
+    ORI_HIP(c0, hipEventSynchronize(cache.read[b.slot]));
+    if (b.mset) {
+      mc->iterations += b.blk;
+      for (size_t j = 0; j < b.act.size(); ++j)
+        ms[b.act[j]]->sc_host[0] = mc->gathered[b.slot * kGroupMaxProblems + j];
+    } else {
+      std::memcpy(c0->sc_host, c0->sc_ring + b.slot * c0->nrhs, c0->nrhs * sizeof(ScalarBlock));
+    }
+    return ORI_OK;
+  };
+
+  Block cur;
+  if (!act.empty()) ORI_TRY(launch_block(act, 0, &cur));
+  while (!act.empty()) {
+    // the next block, on the same members, where every one of them has a
+    // full block of iterations left after this one
+    Block next;
+    bool queued = ahead && cur.one_stream && cur.blk == check_every && !(mc && mc->sets.size() + 1 >= kMultiSetsMax);
+    for (size_t i : cur.act) queued = queued && budget[i] - (*ran)[i] - cur.blk >= check_every;
+    if (queued) ORI_TRY(launch_block(cur.act, cur.blk, &next));
+    ORI_TRY(read_block(cur));
+    std::vector<size_t> left;
+    for (size_t i : cur.act) {
+      (*ran)[i] += cur.blk;
+      trace_cocg(ms[i], prec);
+      if (!all_done(ms[i]) && (*ran)[i] < budget[i]) left.push_back(i);
+    }
+    act.swap(left);
+    if (act.empty()) break;
+    if (queued && act.size() != cur.act.size()) {
+      // a member left: the queued block counts for the others
+      ORI_TRY(read_block(next));
+      std::vector<size_t> still;
+      for (size_t i : act) {
+        (*ran)[i] += next.blk;
+        if (!all_done(ms[i]) && (*ran)[i] < budget[i]) still.push_back(i);
+      }
+      act.swap(still);
+      queued = false;
+      if (act.empty()) break;
+    }
+    if (queued)
+      cur = next;
+    else
+      ORI_TRY(launch_block(act, 0, &cur));
   }
   for (size_t i = 0; i < ms.size(); ++i) {
     if ((*ran)[i] == 0) continue;
@@ -1897,8 +1983,8 @@ ori_status ori_create(const ori_grid* g, int32_t nrhs, int32_t provision, int64_
       return fail(ORI_ERR_DEVICE);
     }
   }
-  // the pinned mirrors of sc and outer_m, one block
-  const size_t sc_bytes = static_cast<size_t>(align_up(R * (int64_t)sizeof(ScalarBlock)));
+  // the pinned mirrors of sc (three of them) and outer_m, one block
+  const size_t sc_bytes = static_cast<size_t>(align_up(3 * R * (int64_t)sizeof(ScalarBlock)));
   if (pool_host_malloc(sc_bytes + 2 * R * sizeof(double), &c->pin_block) != hipSuccess) {
     (void)hipGetLastError();
     set_err(c, ORI_ERR_OUT_OF_MEMORY, "hipHostMalloc of the scalar mirrors failed");
@@ -1906,8 +1992,9 @@ ori_status ori_create(const ori_grid* g, int32_t nrhs, int32_t provision, int64_
   }
   c->pin_bytes = sc_bytes + 2 * R * sizeof(double);
   c->sc_host = static_cast<ScalarBlock*>(c->pin_block);
+  c->sc_ring = c->sc_host + R;
   c->outer_m_host = reinterpret_cast<double*>(static_cast<unsigned char*>(c->pin_block) + sc_bytes);
-  std::memset(c->sc_host, 0, R * sizeof(ScalarBlock));
+  std::memset(c->sc_host, 0, 3 * R * sizeof(ScalarBlock));
   {
     const ori_status ts = shared_twiddles(c->device, L, &c->twd, &c->twf);
     if (ts != ORI_OK) {
@@ -2392,7 +2479,7 @@ void ori_group_destroy(ori_group g) {
   if (!g) return;
   for (ori_ctx c : g->members) (void)hipStreamSynchronize(c->stream);  // nothing of the group in flight
   g->multi.release();  // the graphs, then the tables their nodes point into
-  if (g->multi.gathered) host_pool().give(-1, kGroupMaxProblems * sizeof(ScalarBlock), g->multi.gathered);
+  if (g->multi.gathered) host_pool().give(-1, kGatheredBytes, g->multi.gathered);
   for (ori_ctx c : g->members) ori_destroy(c);
   for (hipStream_t sm : g->streams) {
     (void)hipStreamSynchronize(sm);
