@@ -103,14 +103,16 @@ typedef struct {
                             matvec, except in mixed precision when u = w / S
                             (no S_p small): there the last FP64 refinement
                             residual r = S (u0 - A u) gives it as ||r / S||  */
-  int32_t graph;         /* 1: run each block of check_every COCG iterations as one
-                            replay of a HIP graph, built node by node from the
-                            same kernels and arguments (no stream capture) and
-                            cached per context and precision (the first block,
-                            later blocks; up to 8), so results are bitwise those
-                            of 0: one launch per kernel.  Safe while other threads use
-                            other contexts or the device.  Ignored while
-                            per-kernel profiling is enabled.                       */
+  int32_t graph;         /* 1: a group's problems that launch kernels of their own run
+                            each block of check_every COCG iterations as one
+                            replay of a HIP graph (a chain per problem), built
+                            node by node from the same kernels and arguments (no
+                            stream capture) and cached per group and precision
+                            (up to 8), so results are bitwise those of 0: plain
+                            launches.  A single problem, and problems in common
+                            launches (multi), are launched plainly either way:
+                            the host is a block ahead of its checks, which
+                            measured faster than a replay.                        */
   int32_t multi;         /* ori_group_solve: 1 runs the COCG iterations of the
                             problems still running in one launch per kernel when
                             every one of them has a padded length in 8..256

@@ -203,25 +203,39 @@ __global__ void __launch_bounds__(kRedThreads)
   block_sum4(acc, partials + 4 * (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x));
 }
 
-// One workgroup per right-hand side: reduce its nblk partial quadruples in a
-// fixed order and update its scalars.  1024 threads: after the I1 pass there
-// is one quadruple per I1 workgroup (16 384 at n = 256).
-constexpr int kFinThreads = 1024;
-__device__ __forceinline__ void finalize_body(const double* __restrict__ partials, int64_t nblk, ScalarBlock* scb,
-                                              int64_t rhs, int32_t mode, double eps, double tol2, int32_t tol2_of_bb,
-                                              const double* __restrict__ tol2_rhs) {
-  const double* part = partials + 4 * nblk * rhs;
-  ScalarBlock* sc = scb + rhs;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t i = threadIdx.x; i < nblk; i += kFinThreads) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] += part[4 * i + j];
+// FIN_MU: alpha = rho / mu from the sums {mu.re, mu.im, qq, pp}.  A frozen
+// right-hand side keeps its alpha for k_x_flush (skip).
+struct MuStep {
+  bool skip, breakdown;
+  double re, im;
+};
+__device__ __forceinline__ MuStep mu_step(const ScalarBlock& sc, double s0, double s1, double s2, double s3,
+                                          double eps) {
+  MuStep m{(sc.flags & FLAG_DONE) != 0, false, 0.0, 0.0};
+  if (m.skip || s3 == 0.0) return m;  // s3 = 0: r = p = 0, nothing moves
+  if (hypot(s0, s1) <= eps * sqrt(s2 * s3)) {
+    m.breakdown = true;
+    return m;
   }
-  __shared__ double tot[4];
-  block_sum4<kFinThreads>(acc, tot);
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  const double s0 = tot[0], s1 = tot[1], s2 = tot[2], s3 = tot[3];
+  const double den = s0 * s0 + s1 * s1;
+  m.re = (sc.rho_re * s0 + sc.rho_im * s1) / den;
+  m.im = (sc.rho_im * s0 - sc.rho_re * s1) / den;
+  return m;
+}
+__device__ __forceinline__ void store_mu(ScalarBlock* sc, double s0, double s1, double s2, double s3, MuStep m) {
+  if (m.skip) return;
+  sc->mu_re = s0;
+  sc->mu_im = s1;
+  sc->pp = s3;
+  sc->qq = s2;
+  sc->alpha_re = m.re;
+  sc->alpha_im = m.im;
+}
+
+// The scalars of right-hand side rhs from the sums s0..s3 (one thread).
+__device__ __forceinline__ void finalize_scalars(ScalarBlock* sc, int64_t rhs, double s0, double s1, double s2,
+                                                 double s3, int32_t mode, double eps, double tol2, int32_t tol2_of_bb,
+                                                 const double* __restrict__ tol2_rhs) {
   switch (mode) {
     case FIN_SETUP:
       sc->bb = s0;
@@ -240,6 +254,8 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       sc->alpha_re = 0.0;
       sc->alpha_im = 0.0;
       sc->iters = 0;
+      sc->seq = 0;
+      sc->mu_broken = 0;
       sc->rr_target = (tol2_rhs ? tol2_rhs[rhs] : tol2) * (tol2_of_bb ? sc->bb : s2);
       int f = 0;
       if (s2 == 0.0) f |= FLAG_ZERO_RESIDUAL;
@@ -249,28 +265,15 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
       break;
     }
     case FIN_MU: {
-      if (sc->flags & FLAG_DONE) break;  // frozen: alpha stays for k_x_flush
-      sc->mu_re = s0;
-      sc->mu_im = s1;
-      sc->pp = s3;
-      sc->qq = s2;
-      const double mag = hypot(s0, s1);
-      if (s3 == 0.0) {
-        sc->alpha_re = 0.0;  // r = p = 0: nothing moves
-        sc->alpha_im = 0.0;
-      } else if (mag <= eps * sqrt(s2 * s3)) {
-        sc->flags |= FLAG_BREAKDOWN_MU;
-        sc->alpha_re = 0.0;
-        sc->alpha_im = 0.0;
-      } else {
-        const double den = s0 * s0 + s1 * s1;  // alpha = rho / mu
-        sc->alpha_re = (sc->rho_re * s0 + sc->rho_im * s1) / den;
-        sc->alpha_im = (sc->rho_im * s0 - sc->rho_re * s1) / den;
-      }
+      const MuStep m = mu_step(*sc, s0, s1, s2, s3, eps);
+      store_mu(sc, s0, s1, s2, s3, m);
+      if (m.breakdown) sc->flags |= FLAG_BREAKDOWN_MU;
       break;
     }
     case FIN_RHO: {
       int f = sc->flags;
+      sc->seq += 1;
+      if (!(f & FLAG_DONE) && sc->mu_broken) sc->flags = f |= FLAG_BREAKDOWN_MU;
       if (f & FLAG_DONE) {  // frozen
         sc->beta_re = 0.0;
         sc->beta_im = 0.0;
@@ -303,22 +306,94 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
   }
 }
 
+// One workgroup per right-hand side: reduce its nblk partial quadruples in a
+// fixed order and update its scalars.  1024 threads: after the I1 pass there
+// is one quadruple per I1 workgroup (16 384 at n = 256).
+constexpr int kFinThreads = 1024;
+__device__ __forceinline__ void finalize_body(const double* __restrict__ partials, int64_t nblk, ScalarBlock* scb,
+                                              int64_t rhs, int32_t mode, double eps, double tol2, int32_t tol2_of_bb,
+                                              const double* __restrict__ tol2_rhs, ScalarBlock* ring,
+                                              int64_t ring_stride, int32_t every) {
+  const double* part = partials + 4 * nblk * rhs;
+  ScalarBlock* sc = scb + rhs;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t i = threadIdx.x; i < nblk; i += kFinThreads) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] += part[4 * i + j];
+  }
+  __shared__ double tot[4];
+  block_sum4<kFinThreads>(acc, tot);
+  __syncthreads();
+  if (threadIdx.x == 0) finalize_scalars(sc, rhs, tot[0], tot[1], tot[2], tot[3], mode, eps, tol2, tol2_of_bb, tol2_rhs);
+  if (mode == FIN_RHO && ring) {
+    __syncthreads();
+    static_assert(sizeof(ScalarBlock) % sizeof(double) == 0, "scalar blocks are whole doubles");
+    constexpr int W = static_cast<int>(sizeof(ScalarBlock) / sizeof(double));
+    const int slot = (sc->seq / every) & 1;
+    if (threadIdx.x < W)
+      reinterpret_cast<double*>(ring + slot * ring_stride + rhs)[threadIdx.x] =
+          reinterpret_cast<const double*>(sc)[threadIdx.x];
+  }
+}
+
 __global__ void __launch_bounds__(kFinThreads)
     k_finalize(const double* __restrict__ partials, int64_t nblk, ScalarBlock* scb, int32_t mode, double eps,
-               double tol2, int32_t tol2_of_bb, const double* __restrict__ tol2_rhs) {
-  finalize_body(partials, nblk, scb, blockIdx.x, mode, eps, tol2, tol2_of_bb, tol2_rhs);
+               double tol2, int32_t tol2_of_bb, const double* __restrict__ tol2_rhs, ScalarBlock* ring,
+               int32_t every) {
+  finalize_body(partials, nblk, scb, blockIdx.x, mode, eps, tol2, tol2_of_bb, tol2_rhs, ring, gridDim.x, every);
+}
+
+// FIN_MU inside the update: the sums of nblk <= 1024 quadruples in the order
+// of finalize_body on kFinThreads threads (64 quadruples per wave sum, the
+// waves' sums added in order, the empty ones being zeros), by kRedThreads
+// threads.  Every thread of the workgroup gets them.
+__device__ __forceinline__ void mu_sums(const double* __restrict__ part, int64_t nblk, double (&tot)[4]) {
+  constexpr int G = kFinThreads / 64, NW = kRedThreads / 64;
+  __shared__ double sh[G * 4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int g = w; g < G; g += NW) {
+    const int64_t i = g * 64 + lane;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (g * 64 < nblk) {  // uniform over the wave
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = wave_sum(i < nblk ? 0.0 + part[4 * i + j] : 0.0);
+    }
+    if (lane < 4) sh[g * 4 + lane] = lane == 0 ? v[0] : lane == 1 ? v[1] : lane == 2 ? v[2] : v[3];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    double s = 0.0;
+    for (int g = 0; g < G; ++g) s += sh[g * 4 + j];
+    tot[j] = s;
+  }
 }
 
 // workgroup bid of nb over right-hand side rhs
 template <typename V>
 __device__ __forceinline__ void update_body(cx<V>* __restrict__ x, const cx<V>* __restrict__ p, cx<V>* __restrict__ r,
-                                            const cx<V>* __restrict__ q, int64_t P,
-                                            const ScalarBlock* __restrict__ scb, double* __restrict__ partials,
-                                            int64_t bid, int64_t nb, int64_t rhs) {
-  const ScalarBlock* sc = scb + rhs;
+                                            const cx<V>* __restrict__ q, int64_t P, ScalarBlock* scb,
+                                            double* __restrict__ partials, int64_t bid, int64_t nb, int64_t rhs,
+                                            const double* __restrict__ mu, int64_t mu_nblk, double eps) {
+  ScalarBlock* sc = scb + rhs;
   if (sc->flags & FLAG_DONE) return;  // frozen: FIN_RHO reads no partials either
   const int64_t off = rhs * P;
-  const cxd al = {sc->alpha_re, sc->alpha_im};
+  cxd al;
+  if (mu) {
+    // every workgroup takes the same step; the scalars that the first one
+    // stores are none of those the others read (a breakdown becomes a flag
+    // in FIN_RHO)
+    double tot[4];
+    mu_sums(mu + 4 * mu_nblk * rhs, mu_nblk, tot);
+    const MuStep m = mu_step(*sc, tot[0], tot[1], tot[2], tot[3], eps);
+    if (bid == 0 && threadIdx.x == 0) {
+      store_mu(sc, tot[0], tot[1], tot[2], tot[3], m);
+      sc->mu_broken = m.breakdown ? 1 : 0;
+    }
+    al = cxd{m.re, m.im};
+  } else {
+    al = cxd{sc->alpha_re, sc->alpha_im};
+  }
   const bool moving = al.re != 0.0 || al.im != 0.0;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int64_t i = bid * blockDim.x + threadIdx.x; i < P; i += nb * blockDim.x) {
@@ -342,9 +417,9 @@ __device__ __forceinline__ void update_body(cx<V>* __restrict__ x, const cx<V>* 
 template <typename V>
 __global__ void __launch_bounds__(kRedThreads)
     k_update(cx<V>* __restrict__ x, const cx<V>* __restrict__ p, cx<V>* __restrict__ r,
-             const cx<V>* __restrict__ q, int64_t P, const ScalarBlock* __restrict__ scb,
-             double* __restrict__ partials) {
-  update_body<V>(x, p, r, q, P, scb, partials, blockIdx.x, gridDim.x, blockIdx.y);
+             const cx<V>* __restrict__ q, int64_t P, ScalarBlock* scb, double* __restrict__ partials,
+             const double* __restrict__ mu, int64_t mu_nblk, double eps) {
+  update_body<V>(x, p, r, q, P, scb, partials, blockIdx.x, gridDim.x, blockIdx.y, mu, mu_nblk, eps);
 }
 
 // The finalisation and the update of several problems in one launch
@@ -358,9 +433,11 @@ __device__ __forceinline__ int find_problem(const E* __restrict__ tab, int32_t n
 }
 
 __global__ void __launch_bounds__(kFinThreads)
-    k_multi_finalize(const MultiFin* __restrict__ tab, int32_t np, int32_t mode, double eps) {
+    k_multi_finalize(const MultiFin* __restrict__ tab, int32_t np, int32_t mode, double eps, int64_t ring_stride,
+                     int32_t every) {
   const MultiFin& m = tab[find_problem(tab, np, blockIdx.x)];
-  finalize_body(m.partials, m.nblk, m.sc, blockIdx.x - m.first_block, mode, eps, 0.0, 0, nullptr);
+  finalize_body(m.partials, m.nblk, m.sc, blockIdx.x - m.first_block, mode, eps, 0.0, 0, nullptr, m.ring, ring_stride,
+                every);
 }
 
 // Every guard band of a workspace block in one launch: workgroup i fills
@@ -373,23 +450,11 @@ __global__ void __launch_bounds__(256) k_fill_guards(GuardBands g) {
   band[threadIdx.x] = make_uint4(w, w, w, w);
 }
 
-// The scalar blocks of several problems (one right-hand side each, the sc
-// of each MultiFin entry) copied into out[0..np), host memory the device
-// writes, so that one wait brings every problem's scalars to the host.
-static_assert(sizeof(ScalarBlock) % sizeof(double) == 0, "scalar blocks are whole doubles");
-__global__ void __launch_bounds__(64) k_gather_scalars(const MultiFin* __restrict__ tab, int32_t np, ScalarBlock* out) {
-  constexpr int W = static_cast<int>(sizeof(ScalarBlock) / sizeof(double));
-  for (int i = threadIdx.x; i < np * W; i += blockDim.x) {
-    const int p = i / W, w = i - p * W;
-    reinterpret_cast<double*>(out + p)[w] = reinterpret_cast<const double*>(tab[p].sc)[w];
-  }
-}
-
 template <typename V>
-__global__ void __launch_bounds__(kRedThreads) k_multi_update(const MultiUpd* __restrict__ tab, int32_t np) {
+__global__ void __launch_bounds__(kRedThreads) k_multi_update(const MultiUpd* __restrict__ tab, int32_t np, double eps) {
   const MultiUpd& m = tab[find_problem(tab, np, blockIdx.x)];
   update_body<V>(nullptr, static_cast<const cx<V>*>(m.p), static_cast<cx<V>*>(m.r), static_cast<const cx<V>*>(m.q),
-                 m.P, m.sc, m.partials, blockIdx.x - m.first_block, m.nblocks, 0);
+                 m.P, m.sc, m.partials, blockIdx.x - m.first_block, m.nblocks, 0, m.mu, m.mu_nblk, eps);
 }
 
 template <typename V>
@@ -532,30 +597,31 @@ hipError_t launch_rhs(const void* u0, const void* S, int64_t P, int64_t nrhs, vo
 }
 
 hipError_t launch_finalize(const double* partials, int64_t nblk, int64_t nrhs, ScalarBlock* sc, int32_t mode,
-                           double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, hipStream_t st) {
-  hipError_t e = hipSuccess;
-  e = launch_kernel(k_finalize, dim3(static_cast<unsigned>(nrhs)), dim3(kFinThreads), st, partials, nblk, sc,
-                     mode, eps, tol2, tol2_of_bb, tol2_rhs);
-  return e;
+                           double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, ScalarBlock* ring,
+                           int32_t every, hipStream_t st) {
+  if (ring && every < 1) return hipErrorInvalidValue;
+  return launch_kernel(k_finalize, dim3(static_cast<unsigned>(nrhs)), dim3(kFinThreads), st, partials, nblk, sc, mode,
+                       eps, tol2, tol2_of_bb, tol2_rhs, ring, every);
 }
 
 hipError_t launch_update(int prec, void* x, const void* p, void* r, const void* q, int64_t P, int64_t nrhs,
-                         const ScalarBlock* sc, double* partials, hipStream_t st) {
-  hipError_t e = hipSuccess;
+                         ScalarBlock* sc, double* partials, const double* mu, int64_t mu_nblk, double eps,
+                         hipStream_t st) {
+  if (mu && (mu_nblk < 1 || mu_nblk > kFinThreads)) return hipErrorInvalidValue;
   if (prec == PREC_F64)
-    e = launch_kernel(k_update<double>, red_grid(P, nrhs), dim3(kRedThreads), st, static_cast<cxd*>(x),
-                       static_cast<const cxd*>(p), static_cast<cxd*>(r), static_cast<const cxd*>(q), P, sc, partials);
-  else
-    e = launch_kernel(k_update<float>, red_grid(P, nrhs, kUpdateBlocksMaxF32), dim3(kRedThreads), st, static_cast<cxf*>(x),
-                       static_cast<const cxf*>(p), static_cast<cxf*>(r), static_cast<const cxf*>(q), P, sc, partials);
-  return e;
+    return launch_kernel(k_update<double>, red_grid(P, nrhs), dim3(kRedThreads), st, static_cast<cxd*>(x),
+                         static_cast<const cxd*>(p), static_cast<cxd*>(r), static_cast<const cxd*>(q), P, sc, partials,
+                         mu, mu_nblk, eps);
+  return launch_kernel(k_update<float>, red_grid(P, nrhs, kUpdateBlocksMaxF32), dim3(kRedThreads), st,
+                       static_cast<cxf*>(x), static_cast<const cxf*>(p), static_cast<cxf*>(r),
+                       static_cast<const cxf*>(q), P, sc, partials, mu, mu_nblk, eps);
 }
 
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
-                                 hipStream_t st) {
-  if (np < 1 || blocks < 1) return hipErrorInvalidValue;
+                                 int64_t ring_stride, int32_t every, hipStream_t st) {
+  if (np < 1 || blocks < 1 || every < 1) return hipErrorInvalidValue;
   return launch_kernel(k_multi_finalize, dim3(static_cast<unsigned>(blocks)), dim3(kFinThreads), st, tab, np, mode,
-                       eps);
+                       eps, ring_stride, every);
 }
 
 hipError_t launch_fill_guards(const GuardBands& g, hipStream_t st) {
@@ -566,16 +632,11 @@ hipError_t launch_fill_guards(const GuardBands& g, hipStream_t st) {
   return launch_kernel(k_fill_guards, dim3(static_cast<unsigned>(g.count)), dim3(256), st, g);
 }
 
-hipError_t launch_gather_scalars(const MultiFin* tab, int32_t np, ScalarBlock* out, hipStream_t st) {
-  if (np < 1) return hipErrorInvalidValue;
-  return launch_kernel(k_gather_scalars, dim3(1), dim3(64), st, tab, np, out);
-}
-
-hipError_t launch_multi_update(int prec, const MultiUpd* tab, int32_t np, int64_t blocks, hipStream_t st) {
+hipError_t launch_multi_update(int prec, const MultiUpd* tab, int32_t np, int64_t blocks, double eps, hipStream_t st) {
   if (np < 1 || blocks < 1) return hipErrorInvalidValue;
   if (prec == PREC_F64)
-    return launch_kernel(k_multi_update<double>, dim3(static_cast<unsigned>(blocks)), dim3(kRedThreads), st, tab, np);
-  return launch_kernel(k_multi_update<float>, dim3(static_cast<unsigned>(blocks)), dim3(kRedThreads), st, tab, np);
+    return launch_kernel(k_multi_update<double>, dim3(static_cast<unsigned>(blocks)), dim3(kRedThreads), st, tab, np, eps);
+  return launch_kernel(k_multi_update<float>, dim3(static_cast<unsigned>(blocks)), dim3(kRedThreads), st, tab, np, eps);
 }
 
 hipError_t launch_x_flush(int prec, void* x, const void* p, int64_t P, int64_t nrhs, const ScalarBlock* sc,

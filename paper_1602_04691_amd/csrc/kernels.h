@@ -32,6 +32,8 @@ struct ScalarBlock {
   double s2_min, s2_max;      // min / max |S_p|^2 over the grid (operator coefficients, sc[0])
   int32_t flags;              // FLAG_* below
   int32_t iters;              // COCG iterations done while not converged
+  int32_t seq;                // iterations launched since FIN_INIT, the frozen ones included
+  int32_t mu_broken;          // FIN_MU inside the update met p^T A p ~ 0: FIN_RHO sets the flag
 };
 
 enum : int32_t {
@@ -239,23 +241,26 @@ struct MultiFin {
   int64_t nblk;  // partial quadruples per right-hand side
   ScalarBlock* sc;
   int64_t first_block;
+  ScalarBlock* ring;  // FIN_RHO: where the scalars go on the host (launch_finalize), or NULL
 };
 // COCG update (r -= alpha q, partials) of several problems, one right-hand
-// side each, on their own update_blocks(P, prec) workgroups
+// side each, on their own update_blocks(P, prec) workgroups; mu as in
+// launch_update
 struct MultiUpd {
   const void* p;
   void* r;
   const void* q;
   int64_t P;
-  const ScalarBlock* sc;
+  ScalarBlock* sc;
   double* partials;
   int64_t first_block, nblocks;
+  const double* mu;
+  int64_t mu_nblk;
 };
+// ring_stride: scalar blocks per slot of the rings, every: as launch_finalize
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
-                                 hipStream_t st);
-hipError_t launch_multi_update(int prec, const MultiUpd* tab, int32_t np, int64_t blocks, hipStream_t st);
-// out[p] = *tab[p].sc for p < np; out is host memory the device can write
-hipError_t launch_gather_scalars(const MultiFin* tab, int32_t np, ScalarBlock* out, hipStream_t st);
+                                 int64_t ring_stride, int32_t every, hipStream_t st);
+hipError_t launch_multi_update(int prec, const MultiUpd* tab, int32_t np, int64_t blocks, double eps, hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Elementwise / reduction kernels (aux.hip).  Batched kernels run a grid of
@@ -359,13 +364,28 @@ enum FinalizeMode : int32_t {
 };
 // FIN_INIT: rr_target = t2 * (tol2_of_bb ? bb : rr), t2 = tol2_rhs[rhs] when
 // tol2_rhs is not NULL, else tol2
+// FIN_RHO with ring (memory of the host that the device writes, [2][nrhs]):
+// the scalars also go to slot (seq / every) & 1 of the ring, so that the
+// host needs no copy to read them.
 hipError_t launch_finalize(const double* partials, int64_t nblk, int64_t nrhs, ScalarBlock* sc, int32_t mode,
-                           double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, hipStream_t st);
+                           double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, ScalarBlock* ring,
+                           int32_t every, hipStream_t st);
 // r -= alpha q (and x += alpha p when x is not NULL); partials
 // {r^T r, ||r||^2} on (update_blocks(P, prec), nrhs) workgroups; right-hand
 // sides that are done stay as they are
+// mu (not NULL): FIN_MU is part of this launch: every workgroup reduces the
+// product's mu_nblk <= kMuFusedMax partial quadruples per right-hand side
+// (in the order of launch_finalize: the same bits) and the first one stores
+// the scalars.  partials must not overlap mu.
 hipError_t launch_update(int prec, void* x, const void* p, void* r, const void* q, int64_t P, int64_t nrhs,
-                         const ScalarBlock* sc, double* partials, hipStream_t st);
+                         ScalarBlock* sc, double* partials, const double* mu, int64_t mu_nblk, double eps,
+                         hipStream_t st);
+// The repeated reduction reads (update workgroups) x (quadruples) of 32 bytes;
+// above kMuFusedReads it costs more than the launch it saves (5 us): n = 64
+// with one right-hand side reads 2 MB and gains, with 32 of them 67 MB and
+// loses 0.6 ms of a 13 ms solve.
+constexpr int64_t kMuFusedMax = 512;
+constexpr int64_t kMuFusedReads = int64_t{1} << 16;
 // x += alpha p per right-hand side (the update left pending by the last
 // COCG iteration, whose F1 would have applied it)
 hipError_t launch_x_flush(int prec, void* x, const void* p, int64_t P, int64_t nrhs, const ScalarBlock* sc,

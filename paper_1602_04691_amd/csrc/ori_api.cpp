@@ -255,7 +255,6 @@ struct IterGraph {
     int iters = 0;
     bool first = false;
     std::vector<ori_ctx> members;
-    const void* multi = nullptr;  // the MultiSet its launches serve, or NULL (one chain per member)
   };
   std::vector<Entry> entries;
   hipEvent_t done = nullptr;  // recorded after a replay, waited on by each member's stream
@@ -319,6 +318,7 @@ struct ori_ctx_s {
   ScalarBlock* sc = nullptr;       // [nrhs]
   ScalarBlock* sc_host = nullptr;  // pinned mirror
   ScalarBlock* sc_ring = nullptr;  // pinned, [2][nrhs]: the scalars of the last two blocks of iterations
+  ScalarBlock* sc_ring_dev = nullptr;  // its device address
   double* outer_m = nullptr;       // [2 nrhs]: refinement multipliers, then inner tolerances^2
   double* outer_m_host = nullptr;  // pinned
   // every device workspace is carved from one block (device_pool), the two
@@ -555,8 +555,8 @@ ori_status sync_scalars(ori_ctx c) {
 ori_status finalize(ori_ctx c, int64_t nblk, int mode, double tol2 = 0.0, int tol2_of_bb = 0,
                     const double* tol2_rhs = nullptr) {
   return launch(c, K_FINALIZE, PREC_F64, [&] {
-    return launch_finalize(c->partials, nblk, c->nrhs, c->sc, mode, kBreakdownEps, tol2, tol2_of_bb, tol2_rhs,
-                           c->stream);
+    return launch_finalize(c->partials, nblk, c->nrhs, c->sc, mode, kBreakdownEps, tol2, tol2_of_bb, tol2_rhs, nullptr,
+                           0, c->stream);
   });
 }
 
@@ -754,7 +754,17 @@ bool all_done(ori_ctx c) {
 // S G0 S) p with <p,q>, then alpha, r and rho.  The step x += alpha p of
 // the last iteration is left pending for flush_x.  No memset and no host
 // work, so its launches can also be built into a graph (iteration_graph).
-ori_status cocg_iteration(ori_ctx c, int prec, void* x, void* r, void* p, void* q, const void* S, bool first) {
+// FIN_MU rides in the update where its partials are few (kMuFusedReads); the
+// update's own partials then follow the product's.  every: iterations per
+// check of the host (the ring of launch_finalize).
+bool mu_fused(ori_ctx c, int prec, int64_t i1_blocks) {
+  const int64_t per_rhs = layout_for(c->n, c->nrhs, c->provision).npart / c->nrhs;
+  const int64_t ub = update_blocks(c->P, prec);
+  return i1_blocks <= kMuFusedMax && c->nrhs * ub * i1_blocks <= kMuFusedReads && i1_blocks + ub <= per_rhs;
+}
+
+ori_status cocg_iteration(ori_ctx c, int prec, void* x, void* r, void* p, void* q, const void* S, bool first,
+                          int every) {
   ContigFwdArgs f1{};
   f1.x = r;
   f1.pvec = p;
@@ -766,11 +776,17 @@ ori_status cocg_iteration(ori_ctx c, int prec, void* x, void* r, void* p, void* 
   ContigInvArgs i1 = epi(q, p, 1.0, nullptr, 0.0, S, 1.0, c->partials, 0);
   int64_t nblk = 0;
   ORI_TRY(matvec(c, prec, prec, f1, i1, &nblk));
-  ORI_TRY(finalize(c, nblk, FIN_MU));
+  const bool fused = mu_fused(c, prec, nblk);
+  double* part = c->partials + (fused ? 4 * c->nrhs * nblk : 0);
+  if (!fused) ORI_TRY(finalize(c, nblk, FIN_MU));
   ORI_TRY(launch(c, K_UPDATE, prec, [&] {
-    return launch_update(prec, nullptr, p, r, q, c->P, c->nrhs, c->sc, c->partials, c->stream);
+    return launch_update(prec, nullptr, p, r, q, c->P, c->nrhs, c->sc, part, fused ? c->partials : nullptr, nblk,
+                         kBreakdownEps, c->stream);
   }));
-  return finalize(c, update_blocks(c->P, prec), FIN_RHO);
+  return launch(c, K_FINALIZE, PREC_F64, [&] {
+    return launch_finalize(part, update_blocks(c->P, prec), c->nrhs, c->sc, FIN_RHO, kBreakdownEps, 0.0, 0, nullptr,
+                           c->sc_ring_dev, every, c->stream);
+  });
 }
 
 // The COCG vectors of precision prec of a context (the FFTs run in the same
@@ -784,9 +800,9 @@ PrecVecs vecs(ori_ctx c, int prec) {
   return PrecVecs{c->x, c->r, c->p, c->q, c->S};
 }
 
-ori_status iteration(ori_ctx c, int prec, bool first) {
+ori_status iteration(ori_ctx c, int prec, bool first, int every) {
   const PrecVecs v = vecs(c, prec);
-  return cocg_iteration(c, prec, v.x, v.r, v.p, v.q, v.S, first);
+  return cocg_iteration(c, prec, v.x, v.r, v.p, v.q, v.S, first, every);
 }
 
 // Several contexts solved in lockstep: the members of an ori_group (a
@@ -818,23 +834,17 @@ struct MultiSet {
   const MultiFin* fin_rho = nullptr;
   const MultiUpd* upd = nullptr;
   int64_t fin_blocks = 0, upd_blocks = 0;
+  bool fused = false;  // FIN_MU rides in the update (mu_fused) for every member
 };
 
 // The MultiSets of an ori_group, built on first use and kept (a later
-// solve of the same members reuses them).  Cached graphs of either
-// precision point into them, so they go together: release() drops the
-// group's graphs (graphs[2]) first.
+// solve of the same members reuses them).
 struct MultiCache {
   std::vector<std::unique_ptr<MultiSet>> sets;
-  IterGraph* graphs = nullptr;  // the group's graph caches, [2]
   int64_t iterations = 0;       // COCG iterations run this way (per member set, not per member)
   ScalarBlock* gathered = nullptr;      // pinned, [2][member]: the scalars after even and odd blocks of iterations
   ScalarBlock* gathered_dev = nullptr;  // its device address
   void release() {
-    if (graphs) {
-      graphs[0].release();
-      graphs[1].release();
-    }
     for (auto& m : sets) device_pool().give(m->device, m->dev_bytes, m->dev);
     sets.clear();
   }
@@ -847,7 +857,7 @@ constexpr int32_t kGroupMaxProblems = 64;
 // lengths with multi-problem bodies, one right-hand side each, the tile
 // shape of those bodies, no per-kernel profiling or guard checks
 bool multi_ok(const Members& ms, int prec) {
-  if (ms.size() < 2) return false;
+  if (ms.size() < 2 || ms.size() > static_cast<size_t>(kGroupMaxProblems)) return false;
   const int f = prec == PREC_F32 ? 1 : 0;
   for (ori_ctx c : ms) {
     const Knobs& k = c->knob[f];
@@ -862,6 +872,24 @@ bool multi_ok(const Members& ms, int prec) {
 template <class E>
 size_t table_bytes(size_t n) {
   return (n * sizeof(E) + 255) / 256 * 256;
+}
+
+// The pinned memory that the multi-problem launches write every member's
+// scalars to (the rings of MultiFin, [2][kGroupMaxProblems]).
+constexpr size_t kGatheredBytes = 2 * kGroupMaxProblems * sizeof(ScalarBlock);
+ori_status multi_gathered(MultiCache& mc, ori_ctx c0) {
+  if (mc.gathered) return ORI_OK;
+  if (pool_host_malloc(kGatheredBytes, reinterpret_cast<void**>(&mc.gathered)) != hipSuccess) {
+    mc.gathered = nullptr;
+    return set_err(c0, ORI_ERR_OUT_OF_MEMORY, "hipHostMalloc of the gathered scalars failed");
+  }
+  if (hipHostGetDevicePointer(reinterpret_cast<void**>(&mc.gathered_dev), mc.gathered, 0) != hipSuccess) {
+    host_pool().give(-1, kGatheredBytes, mc.gathered);
+    mc.gathered = nullptr;
+    mc.gathered_dev = nullptr;
+    return set_err(c0, ORI_ERR_DEVICE, "hipHostGetDevicePointer of the gathered scalars failed");
+  }
+  return ORI_OK;
 }
 
 ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSet** out) {
@@ -880,7 +908,12 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
   std::vector<MultiUpd> up(M);
   int64_t first[MP_NPASS] = {};
   bool all = false;  // some length lies between the reserved ones
-  for (ori_ctx c : act) all = all || !reserved_length(static_cast<int>(c->L));
+  ms->fused = true;
+  for (ori_ctx c : act) {
+    all = all || !reserved_length(static_cast<int>(c->L));
+    ms->fused = ms->fused && mu_fused(c, prec, c->K->contig_blocks_per_rhs(c->n * c->n));
+  }
+  ORI_TRY(multi_gathered(mc, c0));
   const MultiKernels* mk = ms->kernels = multi_kernels(prec, all);
   for (size_t i = 0; i < M; ++i) {
     ori_ctx c = act[i];
@@ -918,9 +951,11 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
       ms->blocks[p] = first[p];
     }
     const int64_t ub = update_blocks(c->P, prec);
-    fmu[i] = MultiFin{c->partials, pa.i1_blocks_per_rhs, c->sc, static_cast<int64_t>(i)};
-    frho[i] = MultiFin{c->partials, ub, c->sc, static_cast<int64_t>(i)};
-    up[i] = MultiUpd{v.p, v.r, v.q, c->P, c->sc, c->partials, ms->upd_blocks, ub};
+    const int64_t nblk = pa.i1_blocks_per_rhs;
+    double* part = c->partials + (ms->fused ? 4 * nblk : 0);  // as cocg_iteration
+    fmu[i] = MultiFin{c->partials, nblk, c->sc, static_cast<int64_t>(i), nullptr};
+    frho[i] = MultiFin{part, ub, c->sc, static_cast<int64_t>(i), mc.gathered_dev + i};
+    up[i] = MultiUpd{v.p, v.r, v.q, c->P, c->sc, part, ms->upd_blocks, ub, ms->fused ? c->partials : nullptr, nblk};
     ms->upd_blocks += ub;
   }
   ms->fin_blocks = static_cast<int64_t>(M);
@@ -952,41 +987,20 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
   return ORI_OK;
 }
 
-// The scalar blocks of every member of m gathered into pinned memory (slot 0
-// or 1) by a launch on the first member's stream.
-constexpr size_t kGatheredBytes = 2 * kGroupMaxProblems * sizeof(ScalarBlock);
-ori_status multi_gather_scalars(MultiCache& mc, const MultiSet& m, int slot) {
-  ori_ctx c0 = m.members.front();
-  const int32_t np = static_cast<int32_t>(m.members.size());
-  if (np > kGroupMaxProblems) return set_err(c0, ORI_ERR_INVALID_ARG, "%d problems in one group", np);
-  if (!mc.gathered) {
-    if (pool_host_malloc(kGatheredBytes, reinterpret_cast<void**>(&mc.gathered)) != hipSuccess) {
-      mc.gathered = nullptr;
-      return set_err(c0, ORI_ERR_OUT_OF_MEMORY, "hipHostMalloc of the gathered scalars failed");
-    }
-    if (hipHostGetDevicePointer(reinterpret_cast<void**>(&mc.gathered_dev), mc.gathered, 0) != hipSuccess) {
-      host_pool().give(-1, kGatheredBytes, mc.gathered);
-      mc.gathered = nullptr;
-      mc.gathered_dev = nullptr;
-      return set_err(c0, ORI_ERR_DEVICE, "hipHostGetDevicePointer of the gathered scalars failed");
-    }
-  }
-  ORI_HIP(c0, launch_gather_scalars(m.fin_mu, np, mc.gathered_dev + slot * kGroupMaxProblems, c0->stream));
-  return ORI_OK;
-}
-
 // One COCG iteration of every member of m on stream st: the launches of
 // cocg_iteration, one for all members each.
-ori_status multi_iteration(const MultiSet& m, bool first, hipStream_t st) {
+ori_status multi_iteration(const MultiSet& m, bool first, int every, hipStream_t st) {
   ori_ctx c0 = m.members.front();
   const int32_t np = static_cast<int32_t>(m.members.size());
   for (int p = 0; p < MP_NPASS; ++p) {
     const MultiProblem* tab = (p == MP_F1 && first) ? m.f1_first : m.pass[p];
     ORI_HIP(c0, m.kernels->launch(p, tab, np, m.blocks[p], m.threads[p], m.smem[p], st));
   }
-  ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, st));
-  ORI_HIP(c0, launch_multi_update(m.prec, m.upd, np, m.upd_blocks, st));
-  ORI_HIP(c0, launch_multi_finalize(m.fin_rho, np, m.fin_blocks, FIN_RHO, kBreakdownEps, st));
+  if (!m.fused)
+    ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, 0, every, st));
+  ORI_HIP(c0, launch_multi_update(m.prec, m.upd, np, m.upd_blocks, kBreakdownEps, st));
+  ORI_HIP(c0, launch_multi_finalize(m.fin_rho, np, m.fin_blocks, FIN_RHO, kBreakdownEps, kGroupMaxProblems, every,
+                                    st));
   return ORI_OK;
 }
 
@@ -997,13 +1011,13 @@ ori_status multi_iteration(const MultiSet& m, bool first, hipStream_t st) {
 // exactly the kernels and arguments of its eager launches, in order; the
 // chains of different contexts are independent, so the GPU runs them side
 // by side.  No stream is put into capture mode.
-ori_status iteration_graph(const Members& active, int prec, int iters, bool first, const MultiSet* multi,
-                           IterGraph& cache, hipGraphExec_t* out) {
+ori_status iteration_graph(const Members& active, int prec, int iters, bool first, IterGraph& cache,
+                           hipGraphExec_t* out) {
   *out = nullptr;
   ori_ctx c0 = active.front();
   auto& ents = cache.entries;
   for (size_t i = 0; i < ents.size(); ++i) {
-    if (ents[i].iters == iters && ents[i].first == first && ents[i].members == active && ents[i].multi == multi) {
+    if (ents[i].iters == iters && ents[i].first == first && ents[i].members == active) {
       std::rotate(ents.begin() + i, ents.begin() + i + 1, ents.end());
       *out = ents.back().exec;
       return ORI_OK;
@@ -1018,17 +1032,12 @@ ori_status iteration_graph(const Members& active, int prec, int iters, bool firs
   ORI_HIP(c0, hipGraphCreate(&gb.graph, 0));
   t_graph = &gb;
   ori_status st = ORI_OK;
-  if (multi) {
-    // one chain: the launches of every member together
-    for (int it = 0; it < iters && st == ORI_OK; ++it) st = multi_iteration(*multi, first && it == 0, c0->stream);
-  } else {
-    for (ori_ctx c : active) {
-      gb.last = nullptr;  // a chain of its own
-      for (int it = 0; it < iters && st == ORI_OK; ++it) st = iteration(c, prec, first && it == 0);
-      if (st != ORI_OK) {
-        if (c != c0) set_err(c0, st, "%s", c->err.c_str());
-        break;
-      }
+  for (ori_ctx c : active) {
+    gb.last = nullptr;  // a chain of its own
+    for (int it = 0; it < iters && st == ORI_OK; ++it) st = iteration(c, prec, first && it == 0, iters);
+    if (st != ORI_OK) {
+      if (c != c0) set_err(c0, st, "%s", c->err.c_str());
+      break;
     }
   }
   t_graph = nullptr;
@@ -1042,7 +1051,7 @@ ori_status iteration_graph(const Members& active, int prec, int iters, bool firs
   }
   (void)hipGraphDestroy(gb.graph);
   if (st != ORI_OK) return st;
-  ents.push_back(IterGraph::Entry{exec, iters, first, active, multi});
+  ents.push_back(IterGraph::Entry{exec, iters, first, active});
   *out = exec;
   return ORI_OK;
 }
@@ -1082,11 +1091,8 @@ ori_status sync_members(const Members& ms) {
 // at most budget[i] iterations and leaves when all its right-hand sides are
 // done (a right-hand side that converges or breaks down is frozen on the
 // device, alpha = 0, while the others of its context go on); ran[i]
-// receives the iterations it ran.  Every full block of check_every
-// iterations (the first one starting with the first COCG iteration) is one
-// replay of a graph over the members still running; a shorter block (an
-// iteration budget running out) runs eagerly.  Each member runs exactly the
-// kernels of its own solve, so results do not depend on the other members.
+// receives the iterations it ran.  Each member runs exactly the kernels of
+// its own solve, so results do not depend on the other members.
 //
 // The host reads the scalars of a block while the next one runs: block k + 1
 // is launched before the scalars of block k are waited for, so the GPU does
@@ -1094,16 +1100,22 @@ ori_status sync_members(const Members& ms) {
 // = 32).  Members that block k finished are frozen on the device, and block
 // k + 1 skips them (FLAG_DONE), so the results are those of waiting every
 // time.  This holds where one stream runs the whole block: a single member,
-// or the launches that serve every member (multi_ok).
+// or the launches that serve every member (multi_ok), up to kAheadCells: the
+// skipped block still starts the loads of the strided passes and of I1, 0.9 ms
+// at n = 256, where the 17 round trips of a solve cost 0.25 ms; n = 64 with 32
+// right-hand sides gains 7 %.
+constexpr int64_t kAheadCells = int64_t{1} << 23;
 ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budget, int check_every, bool use_graph,
                       IterGraph& cache, MultiCache* mc, std::vector<int>* ran) {
   ran->assign(ms.size(), 0);
   ORI_TRY(sync_members(ms));
   bool ahead = true;
+  int64_t cells = 0;
   for (ori_ctx c : ms) {
+    cells += c->nrhs * c->P;
     trace_cocg(c, prec);
     use_graph = use_graph && !c->prof && !c->check_guards;
-    ahead = ahead && !c->prof && !c->check_guards && !c->trace;
+    ahead = ahead && cells <= kAheadCells && !c->prof && !c->check_guards && !c->trace;
   }
   std::vector<size_t> act;
   for (size_t i = 0; i < ms.size(); ++i)
@@ -1122,7 +1134,7 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
   // the ones counted in ran
   auto launch_block = [&](const std::vector<size_t>& who, int pending, Block* b) -> ori_status {
     b->act = who;
-    b->slot = count++ & 1;
+    b->slot = ++count & 1;  // as FIN_RHO counts: seq / check_every
     b->blk = check_every;
     for (size_t i : who) b->blk = std::min(b->blk, budget[i] - (*ran)[i] - pending);
     Members active;
@@ -1130,29 +1142,31 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
     // members that fit run in one launch per kernel (multi_ok)
     const MultiSet* mset = nullptr;
     if (mc && multi_ok(active, prec)) {
-      if (mc->sets.size() >= kMultiSetsMax) mc->release();  // with every graph that points into them
+      if (mc->sets.size() >= kMultiSetsMax) mc->release();
       ORI_TRY(multi_set(*mc, active, prec, &mset));
     }
     b->mset = mset;
     b->one_stream = mset || active.size() == 1;
+    // Several members with launches of their own replay a graph with a chain
+    // each.  Where one stream runs the block, plain launches are faster than
+    // a replay (about 12 us less per iteration: n = 32 solve 0.99 -> 0.81 ms,
+    // n = 128 5.0 -> 4.8 ms), because the host is a block ahead.
     hipGraphExec_t exec = nullptr;
-    if (use_graph && b->blk == check_every)
-      ORI_TRY(iteration_graph(active, prec, b->blk, it == 0, mset, cache, &exec));
+    if (use_graph && !b->one_stream && b->blk == check_every)
+      ORI_TRY(iteration_graph(active, prec, b->blk, it == 0, cache, &exec));
     ori_ctx c0 = active.front();
     if (exec) {
       ORI_HIP(c0, hipGraphLaunch(exec, c0->stream));
     } else if (mset) {
-      for (int j = 0; j < b->blk; ++j) ORI_TRY(multi_iteration(*mset, it + j == 0, c0->stream));
+      for (int j = 0; j < b->blk; ++j) ORI_TRY(multi_iteration(*mset, it + j == 0, check_every, c0->stream));
     } else {
       for (int j = 0; j < b->blk; ++j)
-        for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0));
+        for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0, check_every));
     }
-    // the scalars after the block
-    if (mset)
-      ORI_TRY(multi_gather_scalars(*mc, *mset, b->slot));
-    else if (b->one_stream)
-      ORI_HIP(c0, hipMemcpyAsync(c0->sc_ring + b->slot * c0->nrhs, c0->sc, c0->nrhs * sizeof(ScalarBlock),
-                                 hipMemcpyDeviceToHost, c0->stream));
+    // The scalars after a full block are on their way to the rings (FIN_RHO,
+    // slot (blocks so far) & 1); a shorter one, the last of a budget, is read
+    // by sync_members.
+    b->one_stream = b->one_stream && b->blk == check_every;
     if (b->one_stream) {
       hipEvent_t& ev = cache.read[b->slot];
       if (!ev) ORI_HIP(c0, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
@@ -1173,6 +1187,7 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
   // waits for the scalars of a block and brings them to the members' mirrors
   auto read_block = [&](const Block& b) -> ori_status {
     ori_ctx c0 = ms[b.act.front()];
+    if (b.mset) mc->iterations += b.blk;
     if (!b.one_stream) {
       Members active;
       for (size_t i : b.act) active.push_back(ms[i]);
@@ -1180,7 +1195,6 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
     }
     ORI_HIP(c0, hipEventSynchronize(cache.read[b.slot]));
     if (b.mset) {
-      mc->iterations += b.blk;
       for (size_t j = 0; j < b.act.size(); ++j)
         ms[b.act[j]]->sc_host[0] = mc->gathered[b.slot * kGroupMaxProblems + j];
     } else {
@@ -1993,6 +2007,15 @@ ori_status ori_create(const ori_grid* g, int32_t nrhs, int32_t provision, int64_
   c->pin_bytes = sc_bytes + 2 * R * sizeof(double);
   c->sc_host = static_cast<ScalarBlock*>(c->pin_block);
   c->sc_ring = c->sc_host + R;
+  {
+    void* dev = nullptr;
+    if (hipHostGetDevicePointer(&dev, c->pin_block, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      set_err(c, ORI_ERR_DEVICE, "hipHostGetDevicePointer of the scalar mirrors failed");
+      return fail(ORI_ERR_DEVICE);
+    }
+    c->sc_ring_dev = static_cast<ScalarBlock*>(dev) + R;
+  }
   c->outer_m_host = reinterpret_cast<double*>(static_cast<unsigned char*>(c->pin_block) + sc_bytes);
   std::memset(c->sc_host, 0, 3 * R * sizeof(ScalarBlock));
   {
@@ -2359,7 +2382,6 @@ ori_status ori_group_create(const ori_grid* grids, int32_t nprob, int32_t provis
   if (nprob < 1 || nprob > kGroupMaxProblems)
     return set_err(nullptr, ORI_ERR_INVALID_ARG, "nprob = %d out of [1, %d]", nprob, kGroupMaxProblems);
   ori_group g = new ori_group_s();
-  g->multi.graphs = g->graphs;
   g->caller = static_cast<hipStream_t>(stream);
   if (hipGetDevice(&g->device) != hipSuccess || hipEventCreateWithFlags(&g->ready, hipEventDisableTiming) != hipSuccess) {
     (void)hipGetLastError();
@@ -2478,7 +2500,7 @@ ori_status ori_group_multi_iterations(ori_group g, int64_t* iterations) {
 void ori_group_destroy(ori_group g) {
   if (!g) return;
   for (ori_ctx c : g->members) (void)hipStreamSynchronize(c->stream);  // nothing of the group in flight
-  g->multi.release();  // the graphs, then the tables their nodes point into
+  g->multi.release();
   if (g->multi.gathered) host_pool().give(-1, kGatheredBytes, g->multi.gathered);
   for (ori_ctx c : g->members) ori_destroy(c);
   for (hipStream_t sm : g->streams) {
