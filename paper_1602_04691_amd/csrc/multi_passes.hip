@@ -178,11 +178,20 @@ constexpr int max_threads() {
   return t;
 }
 
+// Waves per SIMD that the kernels with the lengths between the reserved ones
+// keep, as the kernels without them have by themselves: complex128 Z three
+// (it would take 174 registers and leave two), the other passes five (104 to
+// 116, four).
+template <typename T, int PASS>
+constexpr int multi_min_waves() {
+  return ORI_MULTI_ALL && sizeof(T) == 8 ? (PASS == MP_Z ? 3 : 5) : 1;
+}
+
 // Launch workgroup b runs workgroup b - first_block of the problem whose
 // range holds it (problems in ascending first_block), on its length's body.
 // The LDS is dynamic: the largest the launch's problems need.
 template <typename T, int PASS>
-__global__ void __launch_bounds__((max_threads<T, PASS>())) k_multi_pass(const MultiProblem* __restrict__ tab,
+__global__ void __launch_bounds__((max_threads<T, PASS>()), (multi_min_waves<T, PASS>())) k_multi_pass(const MultiProblem* __restrict__ tab,
                                                                        int32_t np) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t b = blockIdx.x;
