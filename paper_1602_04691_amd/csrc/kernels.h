@@ -190,8 +190,6 @@ struct MultiProblem {
   int64_t first_block, nblocks;
   int32_t L;
   int32_t ex;    // n = L / 2 exactly (the EX bodies)
-  int32_t soff;  // Z: per-lane plus scalar tile offsets (blk_lg <= the length's alignment)
-  int32_t pad;
   union {
     ContigFwdArgs f1;
     StridedArgs s;
@@ -206,8 +204,8 @@ enum MultiPass : int32_t { MP_F1 = 0, MP_F2 = 1, MP_Z = 2, MP_I2 = 3, MP_I1 = 4,
 // every problem's Z workgroups in the launch).
 constexpr bool multi_length(int L) { return L >= 8 && L <= 256 && radix_plan(L).n > 0; }
 // Their tile shape: wide strided tiles, no Z prefetch, the default Z plan,
-// and Z tiles narrow for complex64 and wide for complex128 (the library's
-// default layout up to L = 256).  A problem whose layout differs runs its
+// and Z tiles narrow for complex64 and wide for complex128 with per-lane
+// addressing (the library's default layout up to L = 256).  A problem whose layout differs runs its
 // own launches.
 constexpr int kMultiZNarrow[2] = {0, 1};  // [PREC_F64, PREC_F32]
 // The multi-problem launches of one precision and set of lengths
@@ -217,9 +215,6 @@ struct MultiKernels {
   // multi-problem bodies, and its LDS bytes
   int (*threads)(int L, int pass);
   int (*smem)(int L, int pass);
-  // whether the Z pass of that length addresses its tiles with scalar offsets
-  // at i1 block 2^e_lg (MultiProblem::soff, as the single-problem launch decides)
-  bool (*z_soff)(int L, int e_lg);
   // tab: device array of np problems (first_block ascending), blocks = the
   // sum of their nblocks; threads and smem = the largest of theirs
   hipError_t (*launch)(int pass, const MultiProblem* tab, int32_t np, int64_t blocks, int threads, int smem,

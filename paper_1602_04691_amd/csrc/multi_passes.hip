@@ -283,19 +283,6 @@ int threads_prec(int L, int pass) {
   }
 }
 
-template <typename T>
-bool soff_prec(int L, int e_lg) {
-  switch (L) {
-#define ORI_SO(Lv) \
-  case Lv:         \
-    return ml##Lv::mz_soff_ok<T>(e_lg);
-    ORI_MULTI_LENGTHS(ORI_SO)
-#undef ORI_SO
-    default:
-      return false;
-  }
-}
-
 }  // namespace
 
 #define ORI_CAT2(a, b, c, d) a##b##c##d
@@ -304,7 +291,7 @@ bool soff_prec(int L, int e_lg) {
 using MT = std::conditional_t<ORI_MULTI_PREC == 64, double, float>;
 
 const MultiKernels* ORI_MULTI_TABLE() {
-  static const MultiKernels k = {threads_prec<MT>, smem_prec<MT>, soff_prec<MT>, launch_prec<MT>};
+  static const MultiKernels k = {threads_prec<MT>, smem_prec<MT>, launch_prec<MT>};
   return &k;
 }
 

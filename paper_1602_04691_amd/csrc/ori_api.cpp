@@ -855,7 +855,7 @@ constexpr int32_t kGroupMaxProblems = 64;
 
 // whether the members can run in one launch per kernel in precision prec:
 // lengths with multi-problem bodies, one right-hand side each, the tile
-// shape of those bodies, no per-kernel profiling or guard checks
+// shape and addressing of those bodies, no per-kernel profiling or guard checks
 bool multi_ok(const Members& ms, int prec) {
   if (ms.size() < 2 || ms.size() > static_cast<size_t>(kGroupMaxProblems)) return false;
   const int f = prec == PREC_F32 ? 1 : 0;
@@ -864,7 +864,7 @@ bool multi_ok(const Members& ms, int prec) {
     if (!multi_length(static_cast<int>(c->L)) || c->nrhs != 1 || c->prof || c->check_guards || k.np_sel != 0 ||
         k.zpf != 0 || k.zplan != 0 || k.z_np != kMultiZNarrow[f])
       return false;
-    if (!reserved_length(static_cast<int>(c->L)) && k.blk_lg > c->K->z_align(prec)) return false;
+    if (k.blk_lg > c->K->z_align(prec)) return false;
   }
   return true;
 }
@@ -934,7 +934,6 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
       e.nblocks = pa.blocks[p];
       e.L = L;
       e.ex = 2 * c->n == c->L;
-      e.soff = mk->z_soff(L, pa.z.e_lg);
       if (p == MP_F1) e.a.f1 = pa.f1;
       if (p == MP_F2) e.a.s = pa.f2;
       if (p == MP_Z) e.a.z = pa.z;
@@ -1307,27 +1306,30 @@ bool valid_knobs(int64_t n, const Knobs& k) {
 // default.
 int default_zplan(int64_t L, int f) { return (L == 1024 && f == 0) ? 1 : 0; }
 
-// The i1 block of B by default: 16 rows up to L = 384; then as measured (one
+// The i1 block of B by default: 16 rows up to L = 384, within the Z pass's
+// per-lane addressing (L = 96: elements 12 rows apart, blocks of four; the
+// 64-bit addressing takes 102 instead of 67 registers); then as measured (one
 // product, blocks 2^2 vs 2^4 in complex128 and 2^3 vs 2^4 in complex64:
 // 1.51 vs 1.58 ms and 0.88 vs 0.89 ms at n = 256), and the largest from L =
 // 768 on, whose rows lie 9 MB and more apart (n = 512: complex64 Z 3.69 vs
-// 4.16 ms, complex128 F2 2.62 vs 2.76 ms).  The lengths between the
-// reserved ones stay within the Z pass's per-lane addressing (L = 720:
-// elements 90 rows apart, blocks of two).
+// 4.16 ms, complex128 F2 2.62 vs 2.76 ms).
 int default_blk_lg(ori_ctx c, int f) {
-  const bool reserved = reserved_length(static_cast<int>(c->L));
   int lg = c->L >= 768 ? 6 : c->L > 384 ? (f ? 3 : 2) : 4;
-  if (!reserved) lg = std::min(lg, c->K->z_align(f ? PREC_F32 : PREC_F64));
+  lg = std::min(lg, c->K->z_align(f ? PREC_F32 : PREC_F64));
   while (lg > 0 && c->n % (int64_t{1} << lg) != 0) --lg;
   return lg;
 }
 
-// Z tiles by default.  The lengths between the reserved ones from L = 576 on:
+// Z tiles by default: complex64 narrow and complex128 narrow from L = 512 on,
+// but a complex64 batch at L <= 128 wide (n = 64 with 32 right-hand sides
+// 0.107 vs 0.136 ms: the pass is bound by memory there, and wide tiles move
+// 128-byte rows).  The lengths between the reserved ones from L = 576 on:
 // complex128 wide (128-byte rows; n = 360 5.24 vs 6.37 ms, n = 320 3.65 vs
 // 3.73 ms), complex64 narrow where narrow tiles are whole wavefronts (n =
 // 320 2.06 vs 2.35 ms, but n = 360 3.10 vs 2.88 ms).
 int default_znarrow(ori_ctx c, int f) {
   const int L = static_cast<int>(c->L);
+  if (f == 1 && L <= 128 && c->nrhs >= 8) return 0;
   if (reserved_length(L) || L < 576) return (f == 1 || L >= 512) ? 1 : 0;
   return f == 1 && 4 * threads_per_pencil(L) % 64 == 0 ? 1 : 0;
 }

@@ -50,7 +50,12 @@ struct RadixPlan {
 // They use radices 6, 9, 10 and 12 to stay at two or three stages; the first
 // radix is even, and the last is 8 or smaller where the length allows it,
 // because the spectrum of the fused Z pass is held in registers in the shape
-// of the last stage.
+// of the last stage.  Plans that read the same both ways (8 x 2 x 8) need one
+// twiddle table for both directions of the Z pass and begin its inverse with
+// the radix 8 butterfly that absorbs the spectrum product: complex64 Z of n =
+// 64 with 32 right-hand sides 0.114 -> 0.106 ms against 8 x 4 x 4 on wide
+// tiles, complex128 Z of n = 96 36.4 -> 31.8 us against 8 x 8 x 3, of n = 128
+// 77.9 -> 71.8 us against 8 x 8 x 4.
 constexpr RadixPlan radix_plan(int L) {
   switch (L) {
     case 2: return {1, {2, 0, 0, 0}};
@@ -64,20 +69,20 @@ constexpr RadixPlan radix_plan(int L) {
     case 24: return {2, {8, 3, 0, 0}};
     case 32: return {2, {8, 4, 0, 0}};
     case 40: return {2, {8, 5, 0, 0}};
-    case 48: return {3, {8, 2, 3, 0}};
+    case 48: return {2, {8, 6, 0, 0}};
     case 64: return {2, {8, 8, 0, 0}};
     case 72: return {2, {8, 9, 0, 0}};
-    case 80: return {3, {8, 2, 5, 0}};
-    case 96: return {3, {8, 4, 3, 0}};
+    case 80: return {2, {8, 10, 0, 0}};
+    case 96: return {2, {8, 12, 0, 0}};
     case 100: return {2, {10, 10, 0, 0}};
     case 108: return {2, {12, 9, 0, 0}};
-    case 128: return {3, {8, 4, 4, 0}};
+    case 128: return {3, {8, 2, 8, 0}};
     case 144: return {2, {12, 12, 0, 0}};
     case 160: return {3, {4, 10, 4, 0}};
-    case 192: return {3, {8, 8, 3, 0}};
+    case 192: return {3, {8, 3, 8, 0}};
     case 200: return {3, {10, 2, 10, 0}};
     case 216: return {3, {6, 6, 6, 0}};
-    case 256: return {3, {8, 8, 4, 0}};
+    case 256: return {3, {8, 4, 8, 0}};
     case 288: return {3, {6, 8, 6, 0}};
     case 320: return {3, {8, 5, 8, 0}};
     case 360: return {3, {6, 10, 6, 0}};
@@ -101,17 +106,18 @@ constexpr RadixPlan radix_plan(int L) {
 // L = 1024 variant 1 is 16 x 8 x 8: two exchanges per transform instead of
 // three with the same 64 threads per pencil (complex128 Z 6.04 vs 6.52 ms
 // at n = 512, its default there; 8 x 16 x 8 on 128 threads, whose 122
-// registers allow twice the wavefronts, takes 6.60 ms).  Lengths without an alternative (L = 64
-// and most short ones) have variant 1 equal to the default.
+// registers allow twice the wavefronts, takes 6.60 ms).  Lengths without an
+// alternative (L = 64 and most short ones) have variant 1 equal to the
+// default.
 constexpr RadixPlan radix_plan(int L, int variant) {
   if (variant == 1) switch (L) {
       case 32: return {2, {4, 8, 0, 0}};
-      case 48: return {3, {8, 3, 2, 0}};
-      case 80: return {3, {8, 5, 2, 0}};
-      case 96: return {3, {4, 8, 3, 0}};
-      case 128: return {3, {4, 4, 8, 0}};
-      case 192: return {3, {8, 3, 8, 0}};
-      case 256: return {3, {4, 8, 8, 0}};
+      case 48: return {3, {8, 2, 3, 0}};
+      case 80: return {3, {8, 2, 5, 0}};
+      case 96: return {3, {8, 4, 3, 0}};
+      case 128: return {3, {8, 4, 4, 0}};
+      case 192: return {3, {8, 8, 3, 0}};
+      case 256: return {3, {8, 8, 4, 0}};
       case 384: return {4, {8, 3, 4, 4}};
       case 512: return {4, {8, 4, 4, 4}};
       case 1024: return {3, {16, 8, 8, 0}};
@@ -157,6 +163,7 @@ constexpr int most_butterflies(int L, const RadixPlan& p) {
 constexpr int threads_per_pencil(int L, int variant = 0) {
   const RadixPlan p = radix_plan(L, variant);
   if (L == 160) return 20;  // 40, 16, 40
+  if (L == 80 || L == 96) return L / 8;  // 10, 8 and 12, 8
   const int lo = fewest_butterflies(L, p), hi = most_butterflies(L, p);
   if (!reserved_length(L) && hi <= 2 * lo && hi != 64) return hi;
   return lo > 128 ? 128 : lo;
