@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(BLOCK_C) k_contig_inv(ContigInvArgs a) {
 }
 
 template <typename T, int NP, bool INV, bool HIN, bool HOUT, bool EX>
-__global__ void __launch_bounds__(block_np<NP>()) k_strided(StridedArgs a) {
+__global__ void __launch_bounds__(block_np<NP>(s_tpp<T>())) k_strided(StridedArgs a) {
   __shared__ __align__(16) unsigned char smem[strided_smem<T, NP>()];
   strided_body<T, NP, INV, HIN, HOUT, EX>(a, blockIdx.x, gridDim.x, smem);
 }
@@ -208,7 +208,7 @@ hipError_t contig_inv(int vp, int fp, const ContigInvArgs& a, hipStream_t st) {
 template <typename T, int NP>
 hipError_t strided_t(const StridedArgs& a, hipStream_t st) {
   hipError_t e = hipSuccess;
-  const dim3 grid(static_cast<unsigned>(a.n_outer * ((a.C + NP - 1) / NP))), block(block_np<NP>());
+  const dim3 grid(static_cast<unsigned>(a.n_outer * ((a.C + NP - 1) / NP))), block(block_np<NP>(s_tpp<T>()));
   if (a.nv < 1 || 2 * a.nv - 1 > L) return hipErrorInvalidValue;
   const bool ex = 2 * a.nv == L;
   if (!a.inverse && a.half_in && !a.half_out)
@@ -231,7 +231,7 @@ hipError_t strided(int fp, const StridedArgs& a, hipStream_t st) {
 // Z workgroups per right-hand-side slice: octant rows m2 in [0, L/2] times
 // the tiles of k3 in [0, L)
 int64_t zpass_blocks(int fprec, int np_sel) {
-  const int64_t np = fprec == PREC_F64 ? np_of<double>(np_sel) : np_of<float>(np_sel);
+  const int64_t np = fprec == PREC_F64 ? z_np<double>(np_sel) : z_np<float>(np_sel);
   return (L / 2 + 1) * ((L + np - 1) / np);
 }
 
@@ -289,8 +289,8 @@ int z_align(int fp) { return fp == PREC_F64 ? z_align_lg<double, 0>() : z_align_
 
 hipError_t zpass(int fp, const ZArgs& a, hipStream_t st) {
   if (a.n < 1 || 2 * a.n - 1 > L || a.kp != L / 2 + 1) return hipErrorInvalidValue;
-  if (fp == PREC_F64) return a.np_sel ? zpass_t<double, np_narrow<double>()>(a, st) : zpass_t<double, nps<double>()>(a, st);
-  return a.np_sel ? zpass_t<float, np_narrow<float>()>(a, st) : zpass_t<float, nps<float>()>(a, st);
+  if (fp == PREC_F64) return a.np_sel ? zpass_t<double, z_np<double>(1)>(a, st) : zpass_t<double, z_np<double>(0)>(a, st);
+  return a.np_sel ? zpass_t<float, z_np<float>(1)>(a, st) : zpass_t<float, z_np<float>(0)>(a, st);
 }
 
 }  // namespace

@@ -109,7 +109,12 @@ constexpr RadixPlan radix_plan(int L) {
 // registers allow twice the wavefronts, takes 6.60 ms).  Lengths without an
 // alternative (L = 64 and most short ones) have variant 1 equal to the
 // default.
+//
+// Variant 2 is not a layout choice: at L = 1024 the complex128 strided passes
+// and the complex64 Z pass run 8 x 16 x 8 on 64 threads per pencil, two exchanges per
+// transform instead of three (every other length: the default).
 constexpr RadixPlan radix_plan(int L, int variant) {
+  if (variant == 2 && L == 1024) return {3, {8, 16, 8, 0}};
   if (variant == 1) switch (L) {
       case 32: return {2, {4, 8, 0, 0}};
       case 48: return {3, {8, 2, 3, 0}};
