@@ -140,6 +140,18 @@ struct ZArgs {
   const ScalarBlock* sc;  // as ContigInvArgs
 };
 
+// F2, Z and I2 of a small problem in one launch, in place on A: one workgroup
+// per (right-hand side, k3) holds its plane (i1, i2) of A in LDS, transforms
+// it along i2 to n x L, runs the Z transforms along i1 column by column, and
+// transforms back (k_plane in passes.hip).
+struct PlaneArgs {
+  void* a;  // A[rhs][i1][i2][k3]
+  int64_t n, nrhs;
+  const void* khat;  // as ZArgs
+  const void* tw;
+  const ScalarBlock* sc;  // as ContigInvArgs
+};
+
 // Kernel spectrum: passes 1 and 2 in place on an octant scratch
 // kh[(m1 kp + m2) kp + m3], kp = n + 1 (the Green's table of the padded grid
 // is even along every axis, so are its transforms, and [0..n] per axis
@@ -172,6 +184,10 @@ struct LengthKernels {
   hipError_t (*spectrum)(const SpectrumArgs&, hipStream_t);
   // largest i1 block (log2) that the Z pass addresses with per-lane offsets
   int (*z_align)(int fprec);
+  // F2, Z and I2 in one launch: whether a plane of this length fits a
+  // workgroup, and the launch
+  bool (*plane_fits)(int fprec);
+  hipError_t (*plane)(int fprec, const PlaneArgs&, hipStream_t);
 };
 
 const LengthKernels* kernels_for_length(int L);

@@ -638,10 +638,28 @@ ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, P
   return ORI_OK;
 }
 
+// Whether F2, Z and I2 run as one launch of planes (PlaneArgs): the plane fits
+// a workgroup, the planes are no more than the CUs, so that each CU has one
+// (kPlanes), the layout is the default one (the plane has its own tiles and
+// the default Z plan; its results are those of the passes bit for bit) and no
+// per-kernel profiling is on.
+constexpr int64_t kPlanes = 256;
+bool plane_launches(ori_ctx c, int fprec) {
+  const Knobs& k = c->knob[fprec == PREC_F32 ? 1 : 0];
+  return k.np_sel == 0 && k.zpf == 0 && k.zplan == 0 && !c->prof && c->L * c->nrhs <= kPlanes &&
+         c->K->plane_fits(fprec);
+}
+
 ori_status matvec(ori_ctx c, int vprec, int fprec, ContigFwdArgs f1, ContigInvArgs i1, int64_t* nblk_out) {
   PassArgs pa;
   ORI_TRY(pass_args(c, fprec, f1, i1, &pa));
   ORI_TRY(launch(c, K_F1, fprec, [&] { return c->K->contig_fwd(vprec, fprec, pa.f1, c->stream); }));
+  if (plane_launches(c, fprec)) {
+    const PlaneArgs p{pa.f1.out, c->n, c->nrhs, pa.z.khat, pa.z.tw, pa.z.sc};
+    ORI_TRY(launch(c, K_Z, fprec, [&] { return c->K->plane(fprec, p, c->stream); }));
+    if (nblk_out) *nblk_out = pa.i1_blocks_per_rhs;
+    return launch(c, K_I1, fprec, [&] { return c->K->contig_inv(vprec, fprec, pa.i1, c->stream); });
+  }
   ORI_TRY(launch(c, K_F2, fprec, [&] { return c->K->strided(fprec, pa.f2, c->stream); }));
   ORI_TRY(launch(c, K_Z, fprec, [&] { return c->K->zpass(fprec, pa.z, c->stream); }));
   ORI_TRY(launch(c, K_I2, fprec, [&] { return c->K->strided(fprec, pa.i2, c->stream); }));

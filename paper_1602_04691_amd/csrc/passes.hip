@@ -60,6 +60,166 @@ __global__ void __launch_bounds__(block_np<NP>(z_tpp<T, PV>()), (z_min_waves<T, 
 }
 
 // ---------------------------------------------------------------------------
+// F2, Z and I2 of a small problem in one launch (PlaneArgs)
+// ---------------------------------------------------------------------------
+// At small n each pass is a launch of 4 to 6 us whose time is the latency of
+// its loads, exchanges and barriers, and A (1 MB at n = 32) stays in L2.  One
+// workgroup per k3 keeps the plane in LDS between the passes: one launch and
+// one round trip to L2 instead of three (one product, complex128: n = 16 30.2
+// -> 25.2 us, n = 32 32.2 -> 30.0 us).  Its 16-byte accesses (one k3 of a row)
+// waste the bandwidth that larger problems and batches are bound by, and one
+// CU has a whole plane to transform: from n = 48 on the three passes are
+// faster (44.2 vs 47.7 us), so lengths above 80 have no plane, and the host
+// uses it while the planes are no more than the CUs (plane_launches).
+//
+// The transforms are those of the separate passes, on the same plans and
+// twiddles, so the results are the same bits.  LDS: the rows of the plane
+// (each row is also the exchange buffer of its own transforms), an exchange
+// buffer for the PC columns of a Z round, and the Z twiddles.
+template <typename T>
+struct Plane {
+  static constexpr int ROWS = (L + 1) / 2;  // n <= L / 2 + 1 / 2
+  static constexpr int ROW = L + L / 8 + 1;  // padded rows, an odd pitch for the columns
+  static constexpr int TP = s_tpp<T>();
+  static_assert(L > 80 || (TP == z_tpp<T, 0>() && z_plan<T, 0>() == 0), "rows and columns share a thread layout");
+  static constexpr int TABLE = ZTwiddles<T, 0>::NTW_F + ZTwiddles<T, 0>::NTW_I;
+  static constexpr int columns(int rounds) { return (L + rounds - 1) / rounds; }
+  static constexpr int64_t bytes(int rounds) {
+    return (int64_t{ROWS} * ROW + int64_t{columns(rounds)} * L + TABLE) * int64_t{sizeof(cx<T>)};
+  }
+  // the fewest rounds of Z columns that fit 1024 threads and the LDS of a CU
+  static constexpr int rounds() {
+    for (int r = 1; r <= 8; ++r)
+      if (block_threads(columns(r) * TP) <= 1024 && bytes(r) <= 160 * 1024) return r;
+    return 0;
+  }
+  static constexpr int RD = rounds();
+  // below 10 the lengths have a single stage and nothing to exchange
+  static constexpr bool FITS = RD > 0 && L >= 10 && L <= 80;
+  static constexpr int PC = FITS ? columns(RD) : 1;
+  static constexpr int THREADS = block_threads(PC * TP);
+  static constexpr bool IDLE = PC * TP % 64 != 0;
+};
+
+template <typename T, bool EX>
+__global__ void __launch_bounds__(Plane<T>::THREADS) k_plane(PlaneArgs a) {
+  using PL = Plane<T>;
+  constexpr int TP = PL::TP, PC = PL::PC, half = L / 2;
+  constexpr int TWM = z_twm<T, 0>();
+  // rows: threads of a row side by side; lanes without a row pass bt = L
+  using RF = Engine<T, L, false, TP, s_plan<T>(), 0, true>;
+  using RI = Engine<T, L, true, TP, s_plan<T>(), 0, true>;
+  using ZF = Engine<T, L, false, TP, 0, TWM, true>;
+  using ZI = Engine<T, L, true, TP, 0, TWM, true>;
+  __shared__ __align__(16) cx<T> plane[PL::ROWS * PL::ROW];
+  __shared__ __align__(16) cx<T> xch[PC * L];
+  __shared__ __align__(16) cx<T> twl[PL::TABLE > 0 ? PL::TABLE : 1];
+  const int tid = threadIdx.x;
+  const int n = static_cast<int>(a.n);
+  const uint32_t rhs = a.nrhs == 1 ? 0u : blockIdx.x / static_cast<uint32_t>(L);
+  const int k3 = static_cast<int>(blockIdx.x - rhs * static_cast<uint32_t>(L));
+  if (a.sc && (a.sc[rhs].flags & FLAG_DONE)) return;
+  const cx<T>* __restrict__ tw = static_cast<const cx<T>*>(a.tw);
+  cx<T>* col = static_cast<cx<T>*>(a.a) + static_cast<int64_t>(rhs) * n * n * L + k3;  // + (i1 n + i2) L
+  ZF::build_stage_table(twl, tw, tid, PL::THREADS);
+  if constexpr (!ZTwiddles<T, 0>::SAME_TW)
+    ZI::build_stage_table(twl + ZTwiddles<T, 0>::NTW_F, tw, tid, PL::THREADS);
+
+  // F2: row i1 of the plane, n inputs, L outputs k2
+  constexpr int RP = PL::THREADS / TP;  // rows at a time
+  const int rt = tid / TP, rb = tid % TP;
+  for (int r0 = 0; r0 < n; r0 += RP) {
+    const int i1 = r0 + rt;
+    const bool act = rt < RP && i1 < n;
+    const int bt = act ? rb : L;
+    const LdsPencil<T> lp{plane + (act ? i1 : 0) * PL::ROW, 1, 1};
+    typename RF::template RegsOf<0> g;
+    RF::template load_first<true>(g, bt, [&](int e) -> cx<T> {
+      if constexpr (!EX) {
+        if (e >= n) return cx<T>{};
+      }
+      return col[(i1 * n + e) * L];
+    });
+    RF::template run<true>(g, bt, lp, tw, [&](auto& gl) {
+      RF::template store_last<KEEP_ALL>(gl, bt, [&](int e, cx<T> v) { lp.template at<0, false>(e) = v; });
+    });
+  }
+  __syncthreads();
+
+  // Z: column k2 along i1, the spectrum of (k2, k3), back to n rows
+  constexpr uint32_t KP = half + 1;
+  const cx<T>* __restrict__ kh = static_cast<const cx<T>*>(a.khat);
+  const uint32_t m3 = static_cast<uint32_t>(k3 <= L - k3 ? k3 : L - k3);
+  const cx<T>* twi = ZTwiddles<T, 0>::SAME_TW ? twl : twl + ZTwiddles<T, 0>::NTW_F;
+  const int ct = tid % PC, cb = tid / PC;
+#pragma unroll 1
+  for (int c0 = 0; c0 < L; c0 += PC) {
+    const int k2 = c0 + ct;
+    const bool act = k2 < L && cb < TP;
+    const int bt = act ? cb : L;
+    const uint32_t m2 = static_cast<uint32_t>(k2 <= L - k2 ? k2 : L - k2);
+    const LdsPencil<T> lp{xch + ct, PC, 0};
+    auto cell = [&](int e) -> cx<T>& { return plane[e * PL::ROW + k2 + (k2 >> 3)]; };
+    typename ZF::template RegsOf<0> g;
+    ZF::template load_first<true>(g, bt, [&](int e) -> cx<T> {
+      if constexpr (!EX) {
+        if (e >= n) return cx<T>{};
+      }
+      return cell(e);
+    });
+    ZRegs<T, 0> kv;
+    auto load_spectrum = [&]() {
+      using St = typename ZF::St;
+      constexpr int SL = St::NS - 1, RL = St::radix(SL);
+#pragma unroll
+      for (int i = 0; i < St::cnt(SL); ++i) {
+        const int b = bt + i * TP;
+        if (b >= St::nbf(SL)) continue;
+#pragma unroll
+        for (int j = 0; j < RL; ++j) {
+          const int e = b + j * (L / RL);
+          const uint32_t m1 = static_cast<uint32_t>(e <= L - e ? e : L - e);
+          kv.v[i][j] = kh[(m1 * KP + m2) * KP + m3];
+        }
+      }
+    };
+    ZF::template run<true>(
+        g, bt, lp, twl,
+        [&](auto& gl) {
+          ZI::run_scaled(gl, kv, bt, lp, twi, [&](auto& gi) {
+            ZI::template store_last<KEEP_HALF>(gi, bt, [&](int e, cx<T> v) {
+              if constexpr (!EX) {
+                if (e >= n) return;
+              }
+              cell(e) = v;
+            });
+          });
+        },
+        load_spectrum);
+  }
+  __syncthreads();
+
+  // I2: row i1 back, n outputs i2
+  for (int r0 = 0; r0 < n; r0 += RP) {
+    const int i1 = r0 + rt;
+    const bool act = rt < RP && i1 < n;
+    const int bt = act ? rb : L;
+    const LdsPencil<T> lp{plane + (act ? i1 : 0) * PL::ROW, 1, 1};
+    typename RI::template RegsOf<0> g;
+    RI::template load_first<false>(g, bt, [&](int e) -> cx<T> { return lp.template at<0, false>(e); });
+    __syncthreads();  // the row is its own exchange buffer
+    RI::template run<false>(g, bt, lp, tw, [&](auto& gl) {
+      RI::template store_last<KEEP_HALF>(gl, bt, [&](int e, cx<T> v) {
+        if constexpr (!EX) {
+          if (e >= n) return;
+        }
+        col[(i1 * n + e) * L] = v;
+      });
+    });
+  }
+}
+
+// ---------------------------------------------------------------------------
 // kernel spectrum on its octant (SpectrumArgs)
 // ---------------------------------------------------------------------------
 // The Green's table on the padded grid: c(m) = G(spacing |d|), wrapped
@@ -285,6 +445,23 @@ hipError_t spectrum(const SpectrumArgs& a, hipStream_t st) {
   return e;
 }
 
+bool plane_fits(int fp) { return fp == PREC_F64 ? Plane<double>::FITS : Plane<float>::FITS; }
+
+template <typename T>
+hipError_t plane_t(const PlaneArgs& a, hipStream_t st) {
+  if constexpr (Plane<T>::FITS) {
+    const dim3 grid(static_cast<unsigned>(L * a.nrhs)), block(Plane<T>::THREADS);
+    return 2 * a.n == L ? launch_kernel((k_plane<T, true>), grid, block, st, a)
+                        : launch_kernel((k_plane<T, false>), grid, block, st, a);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t plane(int fp, const PlaneArgs& a, hipStream_t st) {
+  if (a.n < 1 || 2 * a.n - 1 > L || a.nrhs < 1 || a.nrhs > 4096) return hipErrorInvalidValue;
+  return fp == PREC_F64 ? plane_t<double>(a, st) : plane_t<float>(a, st);
+}
+
 int z_align(int fp) { return fp == PREC_F64 ? z_align_lg<double, 0>() : z_align_lg<float, 0>(); }
 
 hipError_t zpass(int fp, const ZArgs& a, hipStream_t st) {
@@ -300,7 +477,7 @@ hipError_t zpass(int fp, const ZArgs& a, hipStream_t st) {
 
 const LengthKernels* ORI_CAT(kernels_L, ORI_L)() {
   static const LengthKernels k = {L, contig_fwd, contig_inv, strided, zpass, contig_blocks_per_rhs, strided_blocks,
-                                  zpass_blocks, spectrum, z_align};
+                                  zpass_blocks, spectrum, z_align, plane_fits, plane};
   return &k;
 }
 
