@@ -271,7 +271,9 @@ struct MultiUpd {
 // ring_stride: scalar blocks per slot of the rings, every: as launch_finalize
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
                                  int64_t ring_stride, int32_t every, hipStream_t st);
-hipError_t launch_multi_update(int prec, const MultiUpd* tab, int32_t np, int64_t blocks, double eps, hipStream_t st);
+// mu: every entry's mu is set (launch_update), else none is
+hipError_t launch_multi_update(int prec, bool mu, const MultiUpd* tab, int32_t np, int64_t blocks, double eps,
+                               hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Elementwise / reduction kernels (aux.hip).  Batched kernels run a grid of

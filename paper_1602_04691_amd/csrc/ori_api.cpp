@@ -1015,7 +1015,7 @@ ori_status multi_iteration(const MultiSet& m, bool first, int every, hipStream_t
   }
   if (!m.fused)
     ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, 0, every, st));
-  ORI_HIP(c0, launch_multi_update(m.prec, m.upd, np, m.upd_blocks, kBreakdownEps, st));
+  ORI_HIP(c0, launch_multi_update(m.prec, m.fused, m.upd, np, m.upd_blocks, kBreakdownEps, st));
   ORI_HIP(c0, launch_multi_finalize(m.fin_rho, np, m.fin_blocks, FIN_RHO, kBreakdownEps, kGroupMaxProblems, every,
                                     st));
   return ORI_OK;
