@@ -85,9 +85,9 @@ FP64_VECTOR_TFLOPS = 78.6  # MI355X FP64 vector peak (an FMA counts two)
 #   field (eq. 2.10): differences 3, r^2 5, reciprocal square root 1, r 1,
 #     k r 1, sine and cosine 2, 1/(4 pi r) 1, e^{ikr}/(4 pi r) 2, complex
 #     multiply-add with q_p 8  -> 24
-#   far field: beta . x_p 5, k (beta . x_p) 1, sine and cosine 2, complex
-#     multiply-add with q_p 8  -> 16
-FIELD_FLOPS = {"field": 24, "far": 16}
+#   far field: the phase is a product of per-axis phases, so a pair is one
+#     complex multiply-add  -> 8
+FIELD_FLOPS = {"field": 24, "far": 8}
 
 
 def read_profile_value(name, key):

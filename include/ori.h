@@ -115,7 +115,7 @@ typedef struct {
                             measured faster than a replay.                        */
   int32_t multi;         /* ori_group_solve: 1 runs the COCG iterations of the
                             problems still running in one launch per kernel when
-                            every one of them has a padded length in 8..256
+                            every one of them has a padded length up to 256
                             and the default layout, and neither
                             per-kernel profiling nor the guard checks of
                             ORI_CHECK_GUARDS=1 are on (otherwise, and with 0,
@@ -275,13 +275,13 @@ ori_status ori_group_load_all(ori_group g, const double* k, const void* const* h
                               const void* const* u0);
 
 /* Solve every problem (eq. 2.19 by COCG on its complex-symmetric form, as
- * ori_solve).  The problems run in lockstep: each block of check_every
- * COCG iterations of the problems still running is one replay of a HIP
- * graph in which every problem is an independent chain
- * of its own kernels (built node by node, as in ori_solve), so the GPU runs
- * the problems side by side; a problem leaves once it has converged.  Every
- * problem runs exactly the kernels of its own ori_solve, in the same order,
- * so each result is bitwise that of solving the problem alone.
+ * ori_solve).  The problems run in lockstep, check_every COCG iterations at
+ * a time: in one launch per kernel for all problems still running (opts
+ * multi), or as one replay of a HIP graph in which every problem is an
+ * independent chain of its own kernels (opts graph), so the GPU runs the
+ * problems side by side; a problem leaves once it has converged.  Every
+ * problem runs the steps of its own ori_solve, in the same order, so each
+ * result is bitwise that of solving the problem alone.
  *   opts: as ori_solve, the same for every problem (NULL: defaults)
  *   u:    host array of nprob pointers, u[i] device complex128[n_i^3]
  *   info: host array of nprob entries, or NULL

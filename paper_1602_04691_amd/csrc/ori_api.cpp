@@ -1,6 +1,6 @@
 // Host runtime and C ABI (include/ori.h): context, workspaces, the FFT
 // product with the Green's matrix (Section 3), COCG (van der Vorst &
-// Melissen, cited by the paper) with HIP-graph replay of its iterations,
+// Melissen, cited by the paper) with the host a block ahead of its checks,
 // mixed-precision refinement, batches of right-hand sides, the adjoint, the
 // layout autotuner, and the physics of the solution (charges, field, far
 // field, refraction recipe, and the Table 4 comparison of Section 4).
@@ -1851,8 +1851,8 @@ ori_status static_workspace(int dev, void** out) {
 
 // A group of independent problems solved together (ori_group_*).  Each
 // member context has a stream of its own, so the members' eager launches run
-// side by side; their COCG iteration blocks replay one graph with a chain
-// per member.  Group calls start after the work already queued on the
+// side by side; their COCG iteration blocks run in common launches, or as
+// one graph with a chain per member.  Group calls start after the work already queued on the
 // caller's stream (an event) and return after all of theirs is done.
 struct ori_group_s {
   int device = 0;
