@@ -284,8 +284,8 @@ def next_workload(a):
         n = 96
         # one group (the four problems' workspaces and streams), made once like
         # the default workload's context; a step loads every problem and solves
-        # them together: each iteration block of the problems still running is
-        # one graph replay, the problems side by side on the GPU
+        # them together: each iteration of the problems still running is one
+        # launch per kernel, the problems side by side on the GPU
         grp = ori.ori_group_create([p["n"] for p in probs])
         us = [torch.empty(p["n"] ** 3, dtype=torch.complex128, device=dev) for p in probs]
 
@@ -302,7 +302,7 @@ def next_workload(a):
         desc = {"workload": "ori_red_uneven_n32_48_64_96_k5", "n": [32, 48, 64, 96], "k": k,
                 "precision": "mixed", "tol": a.tol, "seeds": [20, 21, 22, 23], "check_every": a.check_every,
                 "solver": "ori_group: the COCG iterations of all running problems in one launch per kernel, "
-                          "each block of check_every iterations one graph replay",
+                          "a block of check_every iterations ahead of the host's check",
                 "group": "made once and loaded with the problems in every step (like an FFT plan); "
                          "solves_per_s_with_group_created_each_step makes and destroys it inside every step"}
     elif a.workload == "gradient":
@@ -465,8 +465,8 @@ def main():
     ap.add_argument("--matvecs", type=int, default=50, help="plain operator applications timed")
     ap.add_argument("--cpu-budget", type=float, default=15.0, help="seconds of oracle rows for cpu_baseline")
     ap.add_argument("--check-every", type=int, default=1,
-                    help="uneven workload: COCG iterations between convergence checks (each block one graph "
-                         "replay); results are bitwise the same for any value (a problem that converges inside "
+                    help="uneven workload: COCG iterations between convergence checks; "
+                         "results are bitwise the same for any value (a problem that converges inside "
                          "a block is frozen on the device), the line also states the rate at the other of 1 and 2")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-mixed", action="store_true")
