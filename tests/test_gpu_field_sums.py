@@ -104,3 +104,28 @@ def test_points_that_are_not_finite():
         v = ori.ori_scattered_field(ctx, one, x).cpu()
     assert v[1] == 0 and torch.isnan(v[4].real) and torch.isfinite(torch.view_as_real(v[[0, 2, 3, 5]])).all()
     assert torch.allclose(v[[0, 2, 3, 5]], v[0].expand(4), rtol=1e-14, atol=0)
+
+
+@pytest.mark.parametrize("far", [False, True])
+def test_sums_that_overflow_or_are_not_finite(far):
+    # the rounding errors that the last additions keep are NaN beside an
+    # infinite sum, which stays infinite; other right-hand sides are unaffected
+    n, k, R = 6, 1e-3, 3
+    P = n ** 3
+    say(f"[field] sums out of range, far={far}")
+    one = torch.ones(P, dtype=torch.complex128, device="cuda")
+    u = one.repeat(R)
+    u[:P] *= 1.7e308  # every term in range, their sum is not
+    u[P + 5] = complex(float("nan"), 0.0)
+    x = torch.tensor([[0.5, 0.5, -0.05], [0.5, 0.5, 1.05]], dtype=torch.float64, device="cuda")
+    if far:
+        x = torch.tensor([[0.0, 0.0, 1.0], [1.0, 0.0, 0.0]], dtype=torch.float64, device="cuda")
+    call = ori.ori_far_field if far else ori.ori_scattered_field
+    with ori.ori_create(n, nrhs=R) as ctx:
+        # h = 8: the far field's sum is before the division by 4 pi
+        ori.ori_load(ctx, k, 8 * one, None, one.repeat(R))
+        v = call(ctx, u, x).view(R, 2).cpu()
+        w = call(ctx, one.repeat(R), x).view(R, 2).cpu()
+    assert torch.isinf(v[0].real).all() and (v[0].real < 0).all()
+    assert torch.isnan(v[1].real).all()
+    assert torch.equal(v[2], w[2]) and torch.isfinite(torch.view_as_real(v[2])).all()
