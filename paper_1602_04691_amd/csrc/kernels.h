@@ -297,7 +297,7 @@ struct FieldArgs {
   double origin[3];
   double corner[6];  // the cube around the cell points: lower, then upper corner
 };
-int64_t field_columns(bool far);
+int64_t field_columns(bool far, int64_t n);
 hipError_t launch_field(const FieldArgs& a, bool far, hipStream_t st);
 // q = -D u over the batch
 hipError_t launch_charges(const void* D, const void* u, int64_t P, int64_t nrhs, void* q, hipStream_t st);

@@ -1715,8 +1715,10 @@ ori_status field_sum(ori_ctx c, const void* u, const double* pts, int64_t M, voi
   a.u = static_cast<const cxd*>(u);
   a.D = c->D;
   a.pts = pts;
-  a.part = c->t1;     // P complex values of scratch,
-  a.part_lo = c->t2;  // and P more
+  // scratch: the idle work arrays of the FFT passes, half for each
+  const int64_t cap = c->nrhs * (c->n * c->n * c->L + c->n * c->L * c->L) / 2;
+  a.part = static_cast<cxd*>(c->arena);
+  a.part_lo = a.part + cap;
   a.out = static_cast<cxd*>(out);
   a.n = c->n;
   a.P = c->P;
@@ -1736,21 +1738,23 @@ ori_status field_sum(ori_ctx c, const void* u, const double* pts, int64_t M, voi
   }
   // Parts: the blocks of columns; their i1 split further (to 8 at least)
   // while the launch has fewer than 2048 workgroups of 4 points, and the
-  // partials [nrhs][points][parts] fit the P-value scratch.
-  const int64_t cblocks = (c->n * c->n + field_columns(far) - 1) / field_columns(far);
+  // partials [nrhs][points][parts] of every point fit the scratch: a second
+  // launch costs more than a second part gains (n = 17 with 2923 points: 149
+  // us for charges and both sums in several launches, 115 us in one each).
+  const int64_t cblocks = (c->n * c->n + field_columns(far, c->n) - 1) / field_columns(far, c->n);
   const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(M, 16384) / 4) * c->nrhs;
   int64_t nch = std::min<int64_t>((2048 + cblocks * groups - 1) / (cblocks * groups), (c->n + 7) / 8);
-  nch = std::max<int64_t>(1, std::min(nch, c->P / (c->nrhs * cblocks)));
+  nch = std::max<int64_t>(1, std::min(nch, cap / (c->nrhs * cblocks * std::min<int64_t>(M, 65535))));
   a.nch = static_cast<int32_t>(nch);
   a.nparts = cblocks * nch;
   // points per launch
-  int64_t mb = c->P / (c->nrhs * a.nparts);
+  int64_t mb = cap / (c->nrhs * a.nparts);
   if (mb < 1) mb = 1;
   if (mb > 65535) mb = 65535;
   for (int64_t m0 = 0; m0 < M; m0 += mb) {
     a.m0 = m0;
     a.mb = std::min(mb, M - m0);
-    if (c->nrhs * a.mb * a.nparts > c->P) return set_err(c, ORI_ERR_UNSUPPORTED, "field scratch too small");
+    if (c->nrhs * a.mb * a.nparts > cap) return set_err(c, ORI_ERR_UNSUPPORTED, "field scratch too small");
     ORI_TRY(launch(c, K_ELEMWISE, PREC_F64, [&] { return launch_field(a, far, c->stream); }));
   }
   ORI_HIP(c, hipStreamSynchronize(c->stream));

@@ -226,10 +226,11 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
 // Far field: the phase of a cell is the product of three axis phases
 // e^{-ik beta_d x_d}, tabulated in LDS per point, so the sum over i1 is one
 // complex multiply-add per pair (4 FP64 operations), and the column's two
-// phases multiply its sum.  A thread takes kFarCols columns, which share each
-// LDS read of an i1 phase, and MP points, which share a cell's charge.
-constexpr int kFarCols = 4;
-template <int MP>
+// phases multiply its sum.  A thread takes COLS columns, which share each
+// LDS read of an i1 phase, and MP points, which share a cell's charge.  COLS
+// is 4, or 2 or 1 where that holds every column of a smaller grid: the rest
+// would be idle lanes (n = 17: 289 columns).
+template <int MP, int COLS>
 __global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
   extern __shared__ __align__(16) unsigned char far_smem[];
   cxd* ph = reinterpret_cast<cxd*>(far_smem);  // [3][n][MP]
@@ -247,19 +248,19 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
   }
   __syncthreads();
   const cxd* __restrict__ u = a.u + rhs * a.P;
-  int cc[kFarCols];
-  double sgn[kFarCols];
+  int cc[COLS];
+  double sgn[COLS];
 #pragma unroll
-  for (int j = 0; j < kFarCols; ++j) {
-    const int col = (cb * kFarCols + j) * kFieldThreads + threadIdx.x;
+  for (int j = 0; j < COLS; ++j) {
+    const int col = (cb * COLS + j) * kFieldThreads + threadIdx.x;
     cc[j] = col < nn ? col : nn - 1;
     sgn[j] = col < nn ? -1.0 : 0.0;
   }
-  cxd acc[MP][kFarCols] = {};
+  cxd acc[MP][COLS] = {};
   for (int i1 = lo; i1 < hi; ++i1) {
-    cxd q[kFarCols];
+    cxd q[COLS];
 #pragma unroll
-    for (int j = 0; j < kFarCols; ++j) {
+    for (int j = 0; j < COLS; ++j) {
       const int64_t p = static_cast<int64_t>(i1) * nn + cc[j];
       q[j] = scale(a.D[p] * u[p], sgn[j]);  // Q_p
     }
@@ -267,14 +268,14 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
     for (int m = 0; m < MP; ++m) {
       const cxd e = ph[i1 * MP + m];
 #pragma unroll
-      for (int j = 0; j < kFarCols; ++j) acc[m][j] = cfma(e, q[j], acc[m][j]);
+      for (int j = 0; j < COLS; ++j) acc[m][j] = cfma(e, q[j], acc[m][j]);
     }
   }
 #pragma unroll
   for (int m = 0; m < MP; ++m) {
     cxd t{0.0, 0.0};
 #pragma unroll
-    for (int j = 0; j < kFarCols; ++j) {
+    for (int j = 0; j < COLS; ++j) {
       const int i2 = cc[j] / n, i3 = cc[j] - i2 * n;
       t = cfma(ph[(n + i2) * MP + m] * ph[(2 * n + i3) * MP + m], acc[m][j], t);
     }
@@ -411,12 +412,14 @@ __global__ void __launch_bounds__(256) k_max(const double* __restrict__ v, int64
 
 }  // namespace
 
-int64_t field_columns(bool far) { return far ? kFarCols * kFieldThreads : kFieldThreads; }
+static int far_cols(int64_t n) { return n * n > 2 * kFieldThreads ? 4 : n * n > kFieldThreads ? 2 : 1; }
+
+int64_t field_columns(bool far, int64_t n) { return far ? far_cols(n) * kFieldThreads : kFieldThreads; }
 
 hipError_t launch_field(const FieldArgs& a, bool far, hipStream_t st) {
   hipError_t e = hipSuccess;
   if (a.n < 1 || a.n > kFieldMaxN || a.n * a.n * a.n != a.P) return hipErrorInvalidValue;  // the axis tables
-  const int64_t cblocks = (a.n * a.n + field_columns(far) - 1) / field_columns(far);
+  const int64_t cblocks = (a.n * a.n + field_columns(far, a.n) - 1) / field_columns(far, a.n);
   if (a.nch < 1 || a.nch > a.n || a.nparts != cblocks * a.nch || a.mb < 1 || a.nrhs > 65535) return hipErrorInvalidValue;
   auto grid = [&](int mp) {
     return dim3(static_cast<unsigned>(a.nparts), static_cast<unsigned>((a.mb + mp - 1) / mp),
@@ -424,10 +427,14 @@ hipError_t launch_field(const FieldArgs& a, bool far, hipStream_t st) {
   };
   const bool wide = a.nparts * ((a.mb + 3) / 4) * a.nrhs >= 1024;
   const unsigned row = static_cast<unsigned>(3 * a.n * sizeof(cxd));  // far: LDS per point
-  if (far && a.n <= kFieldMaxN / 2)
-    e = launch_kernel_smem(k_field_far<4>, grid(4), dim3(kFieldThreads), 4 * row, st, a);
+  if (far && far_cols(a.n) == 1)
+    e = launch_kernel_smem(k_field_far<4, 1>, grid(4), dim3(kFieldThreads), 4 * row, st, a);
+  else if (far && far_cols(a.n) == 2)
+    e = launch_kernel_smem(k_field_far<4, 2>, grid(4), dim3(kFieldThreads), 4 * row, st, a);
+  else if (far && a.n <= kFieldMaxN / 2)
+    e = launch_kernel_smem(k_field_far<4, 4>, grid(4), dim3(kFieldThreads), 4 * row, st, a);
   else if (far)
-    e = launch_kernel_smem(k_field_far<2>, grid(2), dim3(kFieldThreads), 2 * row, st, a);
+    e = launch_kernel_smem(k_field_far<2, 4>, grid(2), dim3(kFieldThreads), 2 * row, st, a);
   else if (wide)
     e = launch_kernel(k_field_near<4>, grid(4), dim3(kFieldThreads), st, a);
   else

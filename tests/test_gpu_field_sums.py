@@ -129,3 +129,10 @@ def test_sums_that_overflow_or_are_not_finite(far):
     assert torch.isinf(v[0].real).all() and (v[0].real < 0).all()
     assert torch.isnan(v[1].real).all()
     assert torch.equal(v[2], w[2]) and torch.isfinite(torch.view_as_real(v[2])).all()
+
+
+@pytest.mark.parametrize("n,M,R", [(1, 40, 1), (2, 150, 1), (3, 400, 2), (16, 11, 1), (22, 37, 1), (23, 4, 2)])
+def test_sums_in_several_launches_and_with_few_columns(n, M, R):
+    # more points than the scratch holds partials for, and the far field's
+    # 1, 2 and 4 columns per thread at their edges (256 and 512 columns)
+    test_sums_against_direct(n, M, R)
