@@ -438,8 +438,8 @@ __global__ void __launch_bounds__(kFinThreads)
     k_multi_finalize(const MultiFin* __restrict__ tab, int32_t np, int32_t mode, double eps, int64_t ring_stride,
                      int32_t every) {
   const MultiFin& m = tab[find_problem(tab, np, blockIdx.x)];
-  finalize_body(m.partials, m.nblk, m.sc, blockIdx.x - m.first_block, mode, eps, 0.0, 0, nullptr, m.ring, ring_stride,
-                every);
+  finalize_body(m.partials, m.nblk, m.sc, blockIdx.x - m.first_block, mode, eps, 0.0, 0, nullptr,
+                every > 0 ? m.ring : nullptr, ring_stride, every);
 }
 
 // Every guard band of a workspace block in one launch: workgroup i fills
@@ -624,7 +624,7 @@ hipError_t launch_update(int prec, void* x, const void* p, void* r, const void* 
 
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
                                  int64_t ring_stride, int32_t every, hipStream_t st) {
-  if (np < 1 || blocks < 1 || every < 1) return hipErrorInvalidValue;
+  if (np < 1 || blocks < 1 || every < 0) return hipErrorInvalidValue;
   return launch_kernel(k_multi_finalize, dim3(static_cast<unsigned>(blocks)), dim3(kFinThreads), st, tab, np, mode,
                        eps, ring_stride, every);
 }

@@ -268,7 +268,8 @@ struct MultiUpd {
   const double* mu;
   int64_t mu_nblk;
 };
-// ring_stride: scalar blocks per slot of the rings, every: as launch_finalize
+// ring_stride: scalar blocks per slot of the rings, every: as launch_finalize,
+// or 0: nothing to the rings
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
                                  int64_t ring_stride, int32_t every, hipStream_t st);
 // mu: every entry's mu is set (launch_update), else none is
@@ -379,7 +380,8 @@ enum FinalizeMode : int32_t {
 // tol2_rhs is not NULL, else tol2
 // FIN_RHO with ring (memory of the host that the device writes, [2][nrhs]):
 // the scalars also go to slot (seq / every) & 1 of the ring, so that the
-// host needs no copy to read them.
+// host needs no copy to read them (given with the last iteration of a block
+// only: the host reads the other slot meanwhile).
 hipError_t launch_finalize(const double* partials, int64_t nblk, int64_t nrhs, ScalarBlock* sc, int32_t mode,
                            double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, ScalarBlock* ring,
                            int32_t every, hipStream_t st);

@@ -773,8 +773,11 @@ bool all_done(ori_ctx c) {
 // the last iteration is left pending for flush_x.  No memset and no host
 // work, so its launches can also be built into a graph (iteration_graph).
 // FIN_MU rides in the update where its partials are few (kMuFusedReads); the
-// update's own partials then follow the product's.  every: iterations per
-// check of the host (the ring of launch_finalize).
+// update's own partials then follow the product's.  every: the last iteration
+// of a full block passes the iterations per check of the host, and its scalars
+// go to the ring (launch_finalize); 0: not to the host.  Writing them in the
+// iterations between as well would reach the slot that the host is reading
+// while the next block runs.
 bool mu_fused(ori_ctx c, int prec, int64_t i1_blocks) {
   const int64_t per_rhs = layout_for(c->n, c->nrhs, c->provision).npart / c->nrhs;
   const int64_t ub = update_blocks(c->P, prec);
@@ -803,7 +806,7 @@ ori_status cocg_iteration(ori_ctx c, int prec, void* x, void* r, void* p, void* 
   }));
   return launch(c, K_FINALIZE, PREC_F64, [&] {
     return launch_finalize(part, update_blocks(c->P, prec), c->nrhs, c->sc, FIN_RHO, kBreakdownEps, 0.0, 0, nullptr,
-                           c->sc_ring_dev, every, c->stream);
+                           every > 0 ? c->sc_ring_dev : nullptr, every, c->stream);
   });
 }
 
@@ -1005,7 +1008,7 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
 }
 
 // One COCG iteration of every member of m on stream st: the launches of
-// cocg_iteration, one for all members each.
+// cocg_iteration, one for all members each.  every: as there.
 ori_status multi_iteration(const MultiSet& m, bool first, int every, hipStream_t st) {
   ori_ctx c0 = m.members.front();
   const int32_t np = static_cast<int32_t>(m.members.size());
@@ -1014,7 +1017,7 @@ ori_status multi_iteration(const MultiSet& m, bool first, int every, hipStream_t
     ORI_HIP(c0, m.kernels->launch(p, tab, np, m.blocks[p], m.threads[p], m.smem[p], st));
   }
   if (!m.fused)
-    ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, 0, every, st));
+    ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, 0, 0, st));
   ORI_HIP(c0, launch_multi_update(m.prec, m.fused, m.upd, np, m.upd_blocks, kBreakdownEps, st));
   ORI_HIP(c0, launch_multi_finalize(m.fin_rho, np, m.fin_blocks, FIN_RHO, kBreakdownEps, kGroupMaxProblems, every,
                                     st));
@@ -1051,7 +1054,7 @@ ori_status iteration_graph(const Members& active, int prec, int iters, bool firs
   ori_status st = ORI_OK;
   for (ori_ctx c : active) {
     gb.last = nullptr;  // a chain of its own
-    for (int it = 0; it < iters && st == ORI_OK; ++it) st = iteration(c, prec, first && it == 0, iters);
+    for (int it = 0; it < iters && st == ORI_OK; ++it) st = iteration(c, prec, first && it == 0, 0);
     if (st != ORI_OK) {
       if (c != c0) set_err(c0, st, "%s", c->err.c_str());
       break;
@@ -1172,18 +1175,22 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
     if (use_graph && !b->one_stream && b->blk == check_every)
       ORI_TRY(iteration_graph(active, prec, b->blk, it == 0, cache, &exec));
     ori_ctx c0 = active.front();
+    // The scalars after a full block go to the rings (its last FIN_RHO, slot
+    // (blocks so far) & 1); a shorter one, the last of a budget, is read by
+    // sync_members.
+    b->one_stream = b->one_stream && b->blk == check_every;
     if (exec) {
       ORI_HIP(c0, hipGraphLaunch(exec, c0->stream));
-    } else if (mset) {
-      for (int j = 0; j < b->blk; ++j) ORI_TRY(multi_iteration(*mset, it + j == 0, check_every, c0->stream));
     } else {
-      for (int j = 0; j < b->blk; ++j)
-        for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0, check_every));
+      for (int j = 0; j < b->blk; ++j) {
+        const int every = b->one_stream && j + 1 == b->blk ? check_every : 0;
+        if (mset) {
+          ORI_TRY(multi_iteration(*mset, it + j == 0, every, c0->stream));
+          continue;
+        }
+        for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0, every));
+      }
     }
-    // The scalars after a full block are on their way to the rings (FIN_RHO,
-    // slot (blocks so far) & 1); a shorter one, the last of a budget, is read
-    // by sync_members.
-    b->one_stream = b->one_stream && b->blk == check_every;
     if (b->one_stream) {
       hipEvent_t& ev = cache.read[b->slot];
       if (!ev) ORI_HIP(c0, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
