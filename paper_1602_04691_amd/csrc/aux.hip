@@ -254,7 +254,6 @@ __device__ __forceinline__ void finalize_scalars(ScalarBlock* sc, int64_t rhs, d
       sc->alpha_re = 0.0;
       sc->alpha_im = 0.0;
       sc->iters = 0;
-      sc->seq = 0;
       sc->mu_broken = 0;
       sc->rr_target = (tol2_rhs ? tol2_rhs[rhs] : tol2) * (tol2_of_bb ? sc->bb : s2);
       int f = 0;
@@ -272,7 +271,6 @@ __device__ __forceinline__ void finalize_scalars(ScalarBlock* sc, int64_t rhs, d
     }
     case FIN_RHO: {
       int f = sc->flags;
-      sc->seq += 1;
       if (!(f & FLAG_DONE) && sc->mu_broken) sc->flags = f |= FLAG_BREAKDOWN_MU;
       if (f & FLAG_DONE) {  // frozen
         sc->beta_re = 0.0;
@@ -312,8 +310,7 @@ __device__ __forceinline__ void finalize_scalars(ScalarBlock* sc, int64_t rhs, d
 constexpr int kFinThreads = 1024;
 __device__ __forceinline__ void finalize_body(const double* __restrict__ partials, int64_t nblk, ScalarBlock* scb,
                                               int64_t rhs, int32_t mode, double eps, double tol2, int32_t tol2_of_bb,
-                                              const double* __restrict__ tol2_rhs, ScalarBlock* ring,
-                                              int64_t ring_stride, int32_t every) {
+                                              const double* __restrict__ tol2_rhs, ScalarBlock* ring) {
   const double* part = partials + 4 * nblk * rhs;
   ScalarBlock* sc = scb + rhs;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -329,18 +326,15 @@ __device__ __forceinline__ void finalize_body(const double* __restrict__ partial
     __syncthreads();
     static_assert(sizeof(ScalarBlock) % sizeof(double) == 0, "scalar blocks are whole doubles");
     constexpr int W = static_cast<int>(sizeof(ScalarBlock) / sizeof(double));
-    const int slot = (sc->seq / every) & 1;
     if (threadIdx.x < W)
-      reinterpret_cast<double*>(ring + slot * ring_stride + rhs)[threadIdx.x] =
-          reinterpret_cast<const double*>(sc)[threadIdx.x];
+      reinterpret_cast<double*>(ring + rhs)[threadIdx.x] = reinterpret_cast<const double*>(sc)[threadIdx.x];
   }
 }
 
 __global__ void __launch_bounds__(kFinThreads)
     k_finalize(const double* __restrict__ partials, int64_t nblk, ScalarBlock* scb, int32_t mode, double eps,
-               double tol2, int32_t tol2_of_bb, const double* __restrict__ tol2_rhs, ScalarBlock* ring,
-               int32_t every) {
-  finalize_body(partials, nblk, scb, blockIdx.x, mode, eps, tol2, tol2_of_bb, tol2_rhs, ring, gridDim.x, every);
+               double tol2, int32_t tol2_of_bb, const double* __restrict__ tol2_rhs, ScalarBlock* ring) {
+  finalize_body(partials, nblk, scb, blockIdx.x, mode, eps, tol2, tol2_of_bb, tol2_rhs, ring);
 }
 
 // FIN_MU inside the update: the sums of nblk <= 1024 quadruples in the order
@@ -435,11 +429,10 @@ __device__ __forceinline__ int find_problem(const E* __restrict__ tab, int32_t n
 }
 
 __global__ void __launch_bounds__(kFinThreads)
-    k_multi_finalize(const MultiFin* __restrict__ tab, int32_t np, int32_t mode, double eps, int64_t ring_stride,
-                     int32_t every) {
+    k_multi_finalize(const MultiFin* __restrict__ tab, int32_t np, int32_t mode, double eps, int64_t ring_at) {
   const MultiFin& m = tab[find_problem(tab, np, blockIdx.x)];
   finalize_body(m.partials, m.nblk, m.sc, blockIdx.x - m.first_block, mode, eps, 0.0, 0, nullptr,
-                every > 0 ? m.ring : nullptr, ring_stride, every);
+                ring_at >= 0 ? m.ring + ring_at : nullptr);
 }
 
 // Every guard band of a workspace block in one launch: workgroup i fills
@@ -600,10 +593,9 @@ hipError_t launch_rhs(const void* u0, const void* S, int64_t P, int64_t nrhs, vo
 
 hipError_t launch_finalize(const double* partials, int64_t nblk, int64_t nrhs, ScalarBlock* sc, int32_t mode,
                            double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, ScalarBlock* ring,
-                           int32_t every, hipStream_t st) {
-  if (ring && every < 1) return hipErrorInvalidValue;
+                           hipStream_t st) {
   return launch_kernel(k_finalize, dim3(static_cast<unsigned>(nrhs)), dim3(kFinThreads), st, partials, nblk, sc, mode,
-                       eps, tol2, tol2_of_bb, tol2_rhs, ring, every);
+                       eps, tol2, tol2_of_bb, tol2_rhs, ring);
 }
 
 template <typename V>
@@ -623,10 +615,10 @@ hipError_t launch_update(int prec, void* x, const void* p, void* r, const void* 
 }
 
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
-                                 int64_t ring_stride, int32_t every, hipStream_t st) {
-  if (np < 1 || blocks < 1 || every < 0) return hipErrorInvalidValue;
+                                 int64_t ring_at, hipStream_t st) {
+  if (np < 1 || blocks < 1) return hipErrorInvalidValue;
   return launch_kernel(k_multi_finalize, dim3(static_cast<unsigned>(blocks)), dim3(kFinThreads), st, tab, np, mode,
-                       eps, ring_stride, every);
+                       eps, ring_at);
 }
 
 hipError_t launch_fill_guards(const GuardBands& g, hipStream_t st) {

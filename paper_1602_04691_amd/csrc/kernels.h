@@ -32,8 +32,8 @@ struct ScalarBlock {
   double s2_min, s2_max;      // min / max |S_p|^2 over the grid (operator coefficients, sc[0])
   int32_t flags;              // FLAG_* below
   int32_t iters;              // COCG iterations done while not converged
-  int32_t seq;                // iterations launched since FIN_INIT, the frozen ones included
   int32_t mu_broken;          // FIN_MU inside the update met p^T A p ~ 0: FIN_RHO sets the flag
+  int32_t pad;
 };
 
 enum : int32_t {
@@ -252,7 +252,7 @@ struct MultiFin {
   int64_t nblk;  // partial quadruples per right-hand side
   ScalarBlock* sc;
   int64_t first_block;
-  ScalarBlock* ring;  // FIN_RHO: where the scalars go on the host (launch_finalize), or NULL
+  ScalarBlock* ring;  // FIN_RHO: the problem's place in slot 0 of the ring (launch_multi_finalize)
 };
 // COCG update (r -= alpha q, partials) of several problems, one right-hand
 // side each, on their own update_blocks(P, prec) workgroups; mu as in
@@ -268,10 +268,10 @@ struct MultiUpd {
   const double* mu;
   int64_t mu_nblk;
 };
-// ring_stride: scalar blocks per slot of the rings, every: as launch_finalize,
-// or 0: nothing to the rings
+// ring_at: FIN_RHO also writes each problem's scalars to ring + ring_at of
+// its entry (as launch_finalize); negative: no ring
 hipError_t launch_multi_finalize(const MultiFin* tab, int32_t np, int64_t blocks, int32_t mode, double eps,
-                                 int64_t ring_stride, int32_t every, hipStream_t st);
+                                 int64_t ring_at, hipStream_t st);
 // mu: every entry's mu is set (launch_update), else none is
 hipError_t launch_multi_update(int prec, bool mu, const MultiUpd* tab, int32_t np, int64_t blocks, double eps,
                                hipStream_t st);
@@ -378,13 +378,11 @@ enum FinalizeMode : int32_t {
 };
 // FIN_INIT: rr_target = t2 * (tol2_of_bb ? bb : rr), t2 = tol2_rhs[rhs] when
 // tol2_rhs is not NULL, else tol2
-// FIN_RHO with ring (memory of the host that the device writes, [2][nrhs]):
-// the scalars also go to slot (seq / every) & 1 of the ring, so that the
-// host needs no copy to read them (given with the last iteration of a block
-// only: the host reads the other slot meanwhile).
+// FIN_RHO with ring (memory of the host that the device writes, [nrhs]): the
+// scalars also go there, so that the host needs no copy to read them.
 hipError_t launch_finalize(const double* partials, int64_t nblk, int64_t nrhs, ScalarBlock* sc, int32_t mode,
                            double eps, double tol2, int32_t tol2_of_bb, const double* tol2_rhs, ScalarBlock* ring,
-                           int32_t every, hipStream_t st);
+                           hipStream_t st);
 // r -= alpha q (and x += alpha p when x is not NULL); partials
 // {r^T r, ||r||^2} on (update_blocks(P, prec), nrhs) workgroups; right-hand
 // sides that are done stay as they are

@@ -556,7 +556,7 @@ ori_status finalize(ori_ctx c, int64_t nblk, int mode, double tol2 = 0.0, int to
                     const double* tol2_rhs = nullptr) {
   return launch(c, K_FINALIZE, PREC_F64, [&] {
     return launch_finalize(c->partials, nblk, c->nrhs, c->sc, mode, kBreakdownEps, tol2, tol2_of_bb, tol2_rhs, nullptr,
-                           0, c->stream);
+                           c->stream);
   });
 }
 
@@ -773,11 +773,8 @@ bool all_done(ori_ctx c) {
 // the last iteration is left pending for flush_x.  No memset and no host
 // work, so its launches can also be built into a graph (iteration_graph).
 // FIN_MU rides in the update where its partials are few (kMuFusedReads); the
-// update's own partials then follow the product's.  every: the last iteration
-// of a full block passes the iterations per check of the host, and its scalars
-// go to the ring (launch_finalize); 0: not to the host.  Writing them in the
-// iterations between as well would reach the slot that the host is reading
-// while the next block runs.
+// update's own partials then follow the product's.  slot: where the scalars go
+// in the ring, 0 or 1, or -1: not to the host.
 bool mu_fused(ori_ctx c, int prec, int64_t i1_blocks) {
   const int64_t per_rhs = layout_for(c->n, c->nrhs, c->provision).npart / c->nrhs;
   const int64_t ub = update_blocks(c->P, prec);
@@ -785,7 +782,7 @@ bool mu_fused(ori_ctx c, int prec, int64_t i1_blocks) {
 }
 
 ori_status cocg_iteration(ori_ctx c, int prec, void* x, void* r, void* p, void* q, const void* S, bool first,
-                          int every) {
+                          int slot) {
   ContigFwdArgs f1{};
   f1.x = r;
   f1.pvec = p;
@@ -806,7 +803,7 @@ ori_status cocg_iteration(ori_ctx c, int prec, void* x, void* r, void* p, void* 
   }));
   return launch(c, K_FINALIZE, PREC_F64, [&] {
     return launch_finalize(part, update_blocks(c->P, prec), c->nrhs, c->sc, FIN_RHO, kBreakdownEps, 0.0, 0, nullptr,
-                           every > 0 ? c->sc_ring_dev : nullptr, every, c->stream);
+                           slot >= 0 ? c->sc_ring_dev + slot * c->nrhs : nullptr, c->stream);
   });
 }
 
@@ -821,9 +818,9 @@ PrecVecs vecs(ori_ctx c, int prec) {
   return PrecVecs{c->x, c->r, c->p, c->q, c->S};
 }
 
-ori_status iteration(ori_ctx c, int prec, bool first, int every) {
+ori_status iteration(ori_ctx c, int prec, bool first, int slot) {
   const PrecVecs v = vecs(c, prec);
-  return cocg_iteration(c, prec, v.x, v.r, v.p, v.q, v.S, first, every);
+  return cocg_iteration(c, prec, v.x, v.r, v.p, v.q, v.S, first, slot);
 }
 
 // Several contexts solved in lockstep: the members of an ori_group (a
@@ -1008,8 +1005,8 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
 }
 
 // One COCG iteration of every member of m on stream st: the launches of
-// cocg_iteration, one for all members each.  every: as there.
-ori_status multi_iteration(const MultiSet& m, bool first, int every, hipStream_t st) {
+// cocg_iteration, one for all members each.  slot: as there.
+ori_status multi_iteration(const MultiSet& m, bool first, int slot, hipStream_t st) {
   ori_ctx c0 = m.members.front();
   const int32_t np = static_cast<int32_t>(m.members.size());
   for (int p = 0; p < MP_NPASS; ++p) {
@@ -1017,10 +1014,10 @@ ori_status multi_iteration(const MultiSet& m, bool first, int every, hipStream_t
     ORI_HIP(c0, m.kernels->launch(p, tab, np, m.blocks[p], m.threads[p], m.smem[p], st));
   }
   if (!m.fused)
-    ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, 0, 0, st));
+    ORI_HIP(c0, launch_multi_finalize(m.fin_mu, np, m.fin_blocks, FIN_MU, kBreakdownEps, -1, st));
   ORI_HIP(c0, launch_multi_update(m.prec, m.fused, m.upd, np, m.upd_blocks, kBreakdownEps, st));
-  ORI_HIP(c0, launch_multi_finalize(m.fin_rho, np, m.fin_blocks, FIN_RHO, kBreakdownEps, kGroupMaxProblems, every,
-                                    st));
+  ORI_HIP(c0, launch_multi_finalize(m.fin_rho, np, m.fin_blocks, FIN_RHO, kBreakdownEps,
+                                    slot >= 0 ? slot * kGroupMaxProblems : -1, st));
   return ORI_OK;
 }
 
@@ -1054,7 +1051,7 @@ ori_status iteration_graph(const Members& active, int prec, int iters, bool firs
   ori_status st = ORI_OK;
   for (ori_ctx c : active) {
     gb.last = nullptr;  // a chain of its own
-    for (int it = 0; it < iters && st == ORI_OK; ++it) st = iteration(c, prec, first && it == 0, 0);
+    for (int it = 0; it < iters && st == ORI_OK; ++it) st = iteration(c, prec, first && it == 0, -1);
     if (st != ORI_OK) {
       if (c != c0) set_err(c0, st, "%s", c->err.c_str());
       break;
@@ -1154,7 +1151,7 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
   // the ones counted in ran
   auto launch_block = [&](const std::vector<size_t>& who, int pending, Block* b) -> ori_status {
     b->act = who;
-    b->slot = ++count & 1;  // as FIN_RHO counts: seq / check_every
+    b->slot = ++count & 1;
     b->blk = check_every;
     for (size_t i : who) b->blk = std::min(b->blk, budget[i] - (*ran)[i] - pending);
     Members active;
@@ -1175,20 +1172,20 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
     if (use_graph && !b->one_stream && b->blk == check_every)
       ORI_TRY(iteration_graph(active, prec, b->blk, it == 0, cache, &exec));
     ori_ctx c0 = active.front();
-    // The scalars after a full block go to the rings (its last FIN_RHO, slot
-    // (blocks so far) & 1); a shorter one, the last of a budget, is read by
-    // sync_members.
+    // The last iteration of a full block writes the scalars to the ring, in
+    // the block's slot: the host reads the other one meanwhile.  A shorter
+    // block, where a member's budget ends, is read by sync_members.
     b->one_stream = b->one_stream && b->blk == check_every;
     if (exec) {
       ORI_HIP(c0, hipGraphLaunch(exec, c0->stream));
     } else {
       for (int j = 0; j < b->blk; ++j) {
-        const int every = b->one_stream && j + 1 == b->blk ? check_every : 0;
+        const int slot = b->one_stream && j + 1 == b->blk ? b->slot : -1;
         if (mset) {
-          ORI_TRY(multi_iteration(*mset, it + j == 0, every, c0->stream));
+          ORI_TRY(multi_iteration(*mset, it + j == 0, slot, c0->stream));
           continue;
         }
-        for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0, every));
+        for (ori_ctx c : active) ORI_TRY(iteration(c, prec, it + j == 0, slot));
       }
     }
     if (b->one_stream) {

@@ -81,3 +81,30 @@ def test_group_blocks_report_what_a_waiting_run_reports(every, prec):
             out.append((us, [report(i) for i in infos]))
         assert out[0][1] == out[1][1]
         assert all(torch.equal(a, b) for a, b in zip(out[0][0], out[1][0]))
+
+
+@pytest.mark.parametrize("every", [2, 4])
+def test_blocks_cut_short_by_one_members_budget(every):
+    # in mixed precision the members' inner iterations differ from the second
+    # cycle on, so a max_iter in between leaves them different budgets: the
+    # block in which the smaller one ends is short, and the others go on with
+    # full blocks whose scalars the host finds all the same
+    ns, ks = (9, 20, 33), (1.0, 5.0, 8.0)
+    say(f"[ahead, budgets] n in {ns} check_every={every}")
+    cases = [workloads.make_case(n, k, seed=60 + n) for n, k in zip(ns, ks)]
+    uneven = 0
+    with ori.ori_group_create(ns) as g:
+        ori.ori_group_load_all(g, ks, [gpu(c["h"]) for c in cases], [gpu(c["N"]) for c in cases],
+                               [gpu(c["u0"]) for c in cases])
+        for max_iter in range(5, 41):
+            out = []
+            for multi in (False, True):
+                us = [torch.empty(n ** 3, dtype=torch.complex128, device="cuda") for n in ns]
+                st, infos = ori.ori_group_solve(g, us, tol=1e-13, precision=1, inner_tol=1e-4, max_iter=max_iter,
+                                                multi=multi, graph=False, check_every=every, raise_on_error=False)
+                out.append((st, [report(i) for i in infos], us))
+            assert out[0][:2] == out[1][:2], max_iter
+            assert all(torch.equal(a, b) for a, b in zip(out[0][2], out[1][2])), max_iter
+            uneven += len({i["iterations"] for i in infos}) > 1 and st != ori.ORI_OK
+    say(f"   {uneven} of 36 runs ended with uneven iterations")
+    assert uneven >= 3
