@@ -412,7 +412,9 @@ hipError_t zpass_s(const ZArgs& a, const dim3& grid, hipStream_t st) {
 
 template <typename T, int NP, int PV>
 hipError_t zpass_p(const ZArgs& a, const dim3& grid, hipStream_t st) {
-  if (a.e_lg <= z_align_lg<T, PV>()) return zpass_s<T, NP, true, PV>(a, grid, st);
+  if constexpr (z_has_soff<T>()) {
+    if (a.e_lg <= z_align_lg<T, PV>()) return zpass_s<T, NP, true, PV>(a, grid, st);
+  }
   return zpass_s<T, NP, false, PV>(a, grid, st);
 }
 
