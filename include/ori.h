@@ -378,8 +378,9 @@ ori_status ori_set_layout(ori_ctx ctx, int32_t precision, const ori_layout* layo
 
 /* Autotuner.  On a loaded context, times the COCG product of each
  * provisioned precision (reps timed products after one warm-up per
- * candidate, reps = 0 means 3) for every valid layout, keeps the fastest on
- * ctx, and records it in a process-wide table keyed by (device, n, nrhs)
+ * candidate, reps = 0 means 3) for every valid layout that runs kernels of
+ * its own (knobs that select nothing at this size stay at their defaults),
+ * keeps the fastest on ctx, and records it in a process-wide table keyed by (device, n, nrhs)
  * from which later ori_create calls on that key start.  Overwrites the
  * context's iterate and work vectors (not its loaded data), so call it
  * between solves.  best[2] and ms_per_product[2] (FP64, complex64; either

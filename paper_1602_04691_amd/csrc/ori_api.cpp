@@ -580,7 +580,38 @@ struct PassArgs {
   int64_t i1_blocks_per_rhs;
 };
 
-ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, PassArgs* out) {
+// Whether F2, Z and I2 run as one launch of planes (PlaneArgs): the plane fits
+// a workgroup, the planes are no more than the CUs, so that each CU has one
+// (kPlanes), the layout is the default one (the plane has its own tiles and
+// the default Z plan; its results are those of the passes bit for bit) and no
+// per-kernel profiling is on.
+constexpr int64_t kPlanes = 256;
+bool plane_layout(ori_ctx c, int fprec, const Knobs& k) {
+  return k.np_sel == 0 && k.zpf == 0 && k.zplan == 0 && !c->prof && c->L * c->nrhs <= kPlanes &&
+         c->K->plane_fits(fprec);
+}
+
+// The layout that the passes run: every knob that selects no kernel here at
+// its default, so that it decides no route either.  The lengths between the
+// reserved ones have no prefetch variant and no second Z plan, and planes have
+// neither i1 blocks nor Z tiles to choose.
+Knobs default_knobs(ori_ctx c, int f);
+Knobs effective_knobs(ori_ctx c, int fprec) {
+  const int f = fprec == PREC_F32 ? 1 : 0;
+  Knobs k = c->knob[f];
+  if (!reserved_length(static_cast<int>(c->L))) k.zpf = 0;
+  if (!has_plan_variant(static_cast<int>(c->L))) k.zplan = 0;
+  if (plane_layout(c, fprec, k)) {
+    const Knobs d = default_knobs(c, f);
+    k.blk_lg = d.blk_lg;
+    k.z_np = d.z_np;
+  }
+  return k;
+}
+bool plane_launches(ori_ctx c, int fprec) { return plane_layout(c, fprec, effective_knobs(c, fprec)); }
+
+// max_lg: the largest i1 block (log2) to use
+ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, PassArgs* out, int max_lg = 6) {
   const int64_t n = c->n, L = c->L, R = c->nrhs;
   const int64_t elem = fprec == PREC_F64 ? 16 : 8;
   char* A = static_cast<char*>(c->arena);
@@ -600,8 +631,8 @@ ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, P
 
   // B layout: i1 split into blocks of 2^lg rows (see ZArgs); the batch is
   // just more outer rows
-  const Knobs& kn = c->knob[fprec == PREC_F32 ? 1 : 0];
-  const int lg = kn.blk_lg;
+  const Knobs kn = effective_knobs(c, fprec);
+  const int lg = std::min(kn.blk_lg, max_lg);
   const int64_t Bk = int64_t{1} << lg;
   const int ns = kn.np_sel;
   // a COCG product skips the right-hand sides that are done
@@ -636,18 +667,6 @@ ori_status pass_args(ori_ctx c, int fprec, ContigFwdArgs f1, ContigInvArgs i1, P
   out->blocks[MP_I2] = c->K->strided_blocks(fprec, ns, R * n, L);
   out->blocks[MP_I1] = R * cb;
   return ORI_OK;
-}
-
-// Whether F2, Z and I2 run as one launch of planes (PlaneArgs): the plane fits
-// a workgroup, the planes are no more than the CUs, so that each CU has one
-// (kPlanes), the layout is the default one (the plane has its own tiles and
-// the default Z plan; its results are those of the passes bit for bit) and no
-// per-kernel profiling is on.
-constexpr int64_t kPlanes = 256;
-bool plane_launches(ori_ctx c, int fprec) {
-  const Knobs& k = c->knob[fprec == PREC_F32 ? 1 : 0];
-  return k.np_sel == 0 && k.zpf == 0 && k.zplan == 0 && !c->prof && c->L * c->nrhs <= kPlanes &&
-         c->K->plane_fits(fprec);
 }
 
 ori_status matvec(ori_ctx c, int vprec, int fprec, ContigFwdArgs f1, ContigInvArgs i1, int64_t* nblk_out) {
@@ -873,16 +892,16 @@ constexpr int32_t kGroupMaxProblems = 64;
 
 // whether the members can run in one launch per kernel in precision prec:
 // lengths with multi-problem bodies, one right-hand side each, the tile
-// shape and addressing of those bodies, no per-kernel profiling or guard checks
+// shape of those bodies, no per-kernel profiling or guard checks (their i1
+// blocks stay within the Z pass's per-lane addressing, multi_set)
 bool multi_ok(const Members& ms, int prec) {
   if (ms.size() < 2 || ms.size() > static_cast<size_t>(kGroupMaxProblems)) return false;
   const int f = prec == PREC_F32 ? 1 : 0;
   for (ori_ctx c : ms) {
-    const Knobs& k = c->knob[f];
+    const Knobs k = effective_knobs(c, prec);
     if (!multi_length(static_cast<int>(c->L)) || c->nrhs != 1 || c->prof || c->check_guards || k.np_sel != 0 ||
         k.zpf != 0 || k.zplan != 0 || k.z_np != kMultiZNarrow[f])
       return false;
-    if (k.blk_lg > c->K->z_align(prec)) return false;
   }
   return true;
 }
@@ -944,7 +963,8 @@ ori_status multi_set(MultiCache& mc, const Members& act, int prec, const MultiSe
     f1.sc = c->sc;
     f1.mode = 1;
     PassArgs pa;
-    ORI_TRY(pass_args(c, prec, f1, epi(v.q, v.p, 1.0, nullptr, 0.0, v.S, 1.0, c->partials, 0), &pa));
+    ORI_TRY(pass_args(c, prec, f1, epi(v.q, v.p, 1.0, nullptr, 0.0, v.S, 1.0, c->partials, 0), &pa,
+                      c->K->z_align(prec)));
     const int L = static_cast<int>(c->L);
     for (int p = 0; p < MP_NPASS; ++p) {
       MultiProblem e{};
@@ -1356,14 +1376,16 @@ int default_znarrow(ori_ctx c, int f) {
   return f == 1 && 4 * threads_per_pencil(L) % 64 == 0 ? 1 : 0;
 }
 
+Knobs default_knobs(ori_ctx c, int f) {
+  Knobs k;
+  k.z_np = default_znarrow(c, f);
+  k.zplan = default_zplan(c->L, f);
+  k.blk_lg = default_blk_lg(c, f);
+  return k;
+}
+
 void choose_layout(ori_ctx c) {
-  for (int f = 0; f < 2; ++f) {
-    Knobs k;
-    k.z_np = default_znarrow(c, f);
-    k.zplan = default_zplan(c->L, f);
-    k.blk_lg = default_blk_lg(c, f);
-    c->knob[f] = k;
-  }
+  for (int f = 0; f < 2; ++f) c->knob[f] = default_knobs(c, f);
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(TuneKey{c->device, c->n, c->nrhs});
@@ -2344,6 +2366,9 @@ ori_status ori_tune(ori_ctx c, int32_t reps, ori_layout* best, double* ms_per_pr
             const Knobs k{lg, np, pf, znp, zp};
             if (!valid_knobs(c->n, k)) continue;
             c->knob[f] = k;
+            // a layout that runs the kernels of another one is not timed:
+            // noise would choose between them
+            if (!(effective_knobs(c, fp) == k)) continue;
             auto product = [&] {
               return matvec(c, fp, fp, plain_f1(x, S), epi(y, x, 1.0, nullptr, 0.0, S, 1.0, nullptr, 0), nullptr);
             };
