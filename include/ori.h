@@ -294,6 +294,10 @@ ori_status ori_group_solve(ori_group g, const ori_solve_opts* opts, void* const*
  * per iteration of the set, since the group was created. */
 ori_status ori_group_multi_iterations(ori_group g, int64_t* iterations);
 
+/* COCG iterations the group's solves have run as replays of a HIP graph
+ * (ori_solve_opts.graph), counted as above. */
+ori_status ori_group_graph_iterations(ori_group g, int64_t* iterations);
+
 /* Release the group and its problems' workspaces (NULL is ignored).  Waits
  * for the group's streams; the workspaces and the streams go to the
  * process-wide cache of ori_destroy. */

@@ -26,7 +26,7 @@ __all__ = [
     "ORI_FP64", "ORI_MIXED", "ORI_OP_SYSTEM", "ORI_OP_SYMMETRIC", "ORI_OP_GREEN",
     "ORI_PROVISION_FP64", "ORI_PROVISION_MIXED", "LIB_PATH", "solve", "solve_many",
     "Group", "ori_group_create", "ori_group_load", "ori_group_load_all", "ori_group_solve", "ori_group_destroy",
-    "ori_group_multi_iterations", "ori_release_cached_memory",
+    "ori_group_multi_iterations", "ori_group_graph_iterations", "ori_release_cached_memory",
 ]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libori.so")
@@ -106,6 +106,7 @@ def lib():
                                                ctypes.POINTER(SolveInfo)]),
             "ori_group_destroy": (None, [P]),
             "ori_group_multi_iterations": (ctypes.c_int, [P, ctypes.POINTER(I64)]),
+            "ori_group_graph_iterations": (ctypes.c_int, [P, ctypes.POINTER(I64)]),
             "ori_load": (ctypes.c_int, [P, D, P, P, P]),
             "ori_spectrum_cache": (ctypes.c_int, [P, I32]),
             "ori_setup": (ctypes.c_int, [ctypes.POINTER(Grid), D, P, P, P, P, ctypes.POINTER(P)]),
@@ -607,6 +608,13 @@ def ori_group_multi_iterations(group):
     """COCG iterations run in one launch per kernel for all running problems."""
     out = ctypes.c_int64()
     _check(lib().ori_group_multi_iterations(group.handle, ctypes.byref(out)))
+    return out.value
+
+
+def ori_group_graph_iterations(group):
+    """COCG iterations run as replays of a HIP graph."""
+    out = ctypes.c_int64()
+    _check(lib().ori_group_graph_iterations(group.handle, ctypes.byref(out)))
     return out.value
 
 

@@ -243,7 +243,8 @@ std::mutex g_tune_mu;
 
 std::map<TuneKey, Tuned> g_tuned;
 
-// Cached HIP graphs of COCG iteration blocks, the most recently used last.
+// Cached HIP graphs of a group's COCG iteration blocks, the most recently used
+// last, and the events of its blocks (also those of a single context).
 // An entry holds `iters` iterations (the first of them the first COCG
 // iteration when `first`) of every context in `members`, one independent
 // chain per context.  A few entries are kept, so that every block shape of
@@ -257,6 +258,7 @@ struct IterGraph {
     std::vector<ori_ctx> members;
   };
   std::vector<Entry> entries;
+  int64_t iterations = 0;     // COCG iterations run by replays (per replay, not per member)
   hipEvent_t done = nullptr;  // recorded after a replay, waited on by each member's stream
   // recorded after the copies of the scalars of a block of iterations, for
   // even and odd blocks (group_cocg)
@@ -336,7 +338,8 @@ struct ori_ctx_s {
   // right-hand side on stderr after every check of a solve
   bool trace = false;
 
-  // COCG iteration blocks as HIP graphs, one per vector precision
+  // per vector precision: the events of the blocks of iterations (a single
+  // context launches them plainly, its groups hold the graphs)
   IterGraph graphs[2];
 
   // profiling
@@ -1198,6 +1201,7 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
     b->one_stream = b->one_stream && b->blk == check_every;
     if (exec) {
       ORI_HIP(c0, hipGraphLaunch(exec, c0->stream));
+      cache.iterations += b->blk;
     } else {
       for (int j = 0; j < b->blk; ++j) {
         const int slot = b->one_stream && j + 1 == b->blk ? b->slot : -1;
@@ -2548,6 +2552,13 @@ ori_status ori_group_multi_iterations(ori_group g, int64_t* iterations) {
   if (!g) return set_err(nullptr, ORI_ERR_INVALID_ARG, "group is NULL");
   if (!iterations) return set_err(nullptr, ORI_ERR_INVALID_ARG, "iterations is NULL");
   *iterations = g->multi.iterations;
+  return ORI_OK;
+}
+
+ori_status ori_group_graph_iterations(ori_group g, int64_t* iterations) {
+  if (!g) return set_err(nullptr, ORI_ERR_INVALID_ARG, "group is NULL");
+  if (!iterations) return set_err(nullptr, ORI_ERR_INVALID_ARG, "iterations is NULL");
+  *iterations = g->graphs[0].iterations + g->graphs[1].iterations;
   return ORI_OK;
 }
 
