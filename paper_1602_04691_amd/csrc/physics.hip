@@ -126,8 +126,9 @@ __device__ __forceinline__ cxd turn(double th, double tl, const cxd* __restrict_
 // k r in units of 1/kTurn turns as an unevaluated sum of two doubles (4: the
 // product's rounding error is kept, so the phase is as good as r itself),
 // its e^{i..} (14, above) and the sum (6).  Points so far away that the
-// phase would pass 2^50 take the library's sincos.  MP points share a cell's
-// loads and charge: 4 where that leaves 1024 workgroups, else 1.
+// phase would pass 2^50 take the library's sincos in a loop of their own, so
+// that a point's value does not depend on the others of its group.  MP points
+// share a cell's loads and charge: 4 where that leaves 1024 workgroups, else 1.
 template <int MP>
 __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
   __shared__ double x1[kFieldMaxN];
@@ -150,7 +151,7 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
   const int i2 = cc / n, i3 = cc - i2 * n;
   const double x2 = cell_coord(a, 1, i2), x3 = cell_coord(a, 2, i3);
   double y0[MP], s23[MP];
-  bool fast = true;
+  bool lib[MP], any_lib = false, all_lib = true;
 #pragma unroll
   for (int m = 0; m < MP; ++m) {
     const int64_t pm = m0 + m < a.mb ? m0 + m : a.mb - 1;
@@ -165,7 +166,9 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
       const double u = fabs(y[d] - a.corner[d]), v = fabs(y[d] - a.corner[3 + d]);
       far2 += u > v || !(u <= v) ? u * u : v * v;
     }
-    fast = fast && far2 * a.kt_hi * a.kt_hi < 0x1p100 && far2 < 0x1p1000;
+    lib[m] = !(far2 * a.kt_hi * a.kt_hi < 0x1p100 && far2 < 0x1p1000);
+    any_lib = any_lib || lib[m];
+    all_lib = all_lib && lib[m];
   }
   __syncthreads();
   const cxd* __restrict__ u = a.u + rhs * a.P;
@@ -175,7 +178,11 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
   const double sg = act ? -1.0 / kFourPi : 0.0;
   const cxd* __restrict__ Dc = a.D + cc;
   const cxd* __restrict__ uc = u + cc;
-  cxd dn = Dc[static_cast<int64_t>(lo) * nn], un = uc[static_cast<int64_t>(lo) * nn];
+  cxd dn, un;
+  auto first_q = [&]() {
+    dn = Dc[static_cast<int64_t>(lo) * nn];
+    un = uc[static_cast<int64_t>(lo) * nn];
+  };
   auto next_q = [&](int i1) -> cxd {
     const cxd q = scale(dn * un, sg);
     const int64_t p = static_cast<int64_t>(i1 + 1 < hi ? i1 + 1 : i1) * nn;
@@ -183,7 +190,8 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
     un = uc[p];
     return q;
   };
-  if (fast) {
+  if (!all_lib) {
+    first_q();
     for (int i1 = lo; i1 < hi; ++i1) {
       const cxd q = next_q(i1);
       const double x = x1[i1];
@@ -199,12 +207,18 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
         acc[m] = cfma(e, w, acc[m]);
       }
     }
-  } else {
+  }
+  if (any_lib) {
+#pragma unroll
+    for (int m = 0; m < MP; ++m)
+      if (lib[m]) acc[m] = cxd{0.0, 0.0};
+    first_q();
     for (int i1 = lo; i1 < hi; ++i1) {
       const cxd q = next_q(i1);
       const double x = x1[i1];
 #pragma unroll
       for (int m = 0; m < MP; ++m) {
+        if (!lib[m]) continue;
         const double d0 = y0[m] - x;
         const double rsq = d0 * d0 + s23[m];
         if (rsq > 0.0) {

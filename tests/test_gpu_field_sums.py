@@ -106,6 +106,35 @@ def test_points_that_are_not_finite():
     assert torch.allclose(v[[0, 2, 3, 5]], v[0].expand(4), rtol=1e-14, atol=0)
 
 
+@pytest.mark.parametrize("n,M", [(64, 400), (16, 4100), (6, 9)])
+def test_points_keep_their_values_beside_far_and_nan_points(n, M):
+    # four points to a thread (n = 64: 16 blocks of columns, n = 16: one) and one
+    # (the last case): among the points are NaN, infinite and very far ones, at
+    # every place of a group; the others give the bits they give without them
+    k = 3.1
+    say(f"[field] n={n} M={M} with far and NaN points among them")
+    g = torch.Generator(device="cuda").manual_seed(n + M)
+    P = n ** 3
+    u = torch.complex(torch.randn(P, dtype=torch.float64, device="cuda", generator=g),
+                      torch.randn(P, dtype=torch.float64, device="cuda", generator=g))
+    x = 1.5 + torch.rand(M, 3, dtype=torch.float64, device="cuda", generator=g)
+    y = x.clone()
+    odd = torch.arange(0, M, 5, device="cuda")  # 0, 1, 2, 3 in the groups of four
+    y[odd[0::3], 1] = float("nan")
+    y[odd[1::3], 2] = 1e18
+    y[odd[2::3], 0] = -float("inf")
+    keep = torch.ones(M, dtype=torch.bool, device="cuda")
+    keep[odd] = False
+    one = torch.ones(P, dtype=torch.complex128, device="cuda")
+    with ori.ori_create(n) as ctx:
+        ori.ori_load(ctx, k, one, None, one)
+        v, w = ori.ori_scattered_field(ctx, u, x), ori.ori_scattered_field(ctx, u, y)
+        few = ori.ori_scattered_field(ctx, u, y[odd[1::3]].contiguous())
+    assert torch.equal(v[keep], w[keep])
+    assert (w[odd[0::3]] == 0).all() and torch.isnan(w[odd[2::3]].real).all()
+    assert torch.allclose(w[odd[1::3]], few, rtol=1e-12, atol=0)
+
+
 @pytest.mark.parametrize("far", [False, True])
 def test_sums_that_overflow_or_are_not_finite(far):
     # the rounding errors that the last additions keep are NaN beside an
