@@ -120,15 +120,21 @@ __device__ __forceinline__ cxd turn(double th, double tl, const cxd* __restrict_
   return {fmadd(r.re, c1, fmadd(-r.im, s, r.re)), fmadd(r.im, c1, fmadd(r.re, s, r.im))};
 }
 
+// squared distances from here on take fast_rsqrt
+constexpr double kNearSq = 0x1p-900;
+
 // Field: grid (parts, groups of MP points, right-hand sides), part =
-// (block of 256 columns, range of i1).  Per pair: the distance (3
+// (block of 256 columns, range of i1).  Per pair: the distance (2
 // operations: the column's share of r^2 is kept), 1/r (6), r and the phase
 // k r in units of 1/kTurn turns as an unevaluated sum of two doubles (4: the
 // product's rounding error is kept, so the phase is as good as r itself),
-// its e^{i..} (14, above) and the sum (6).  Points so far away that the
-// phase would pass 2^50 take the library's sincos in a loop of their own, so
-// that a point's value does not depend on the others of its group.  MP points
-// share a cell's loads and charge: 4 where that leaves 1024 workgroups, else 1.
+// its e^{i..} (14, above) and the sum (6).  A cell at the point itself is left
+// out, whatever its charge: the waves that hold such a column test each
+// distance, which changes no other bit.  Points so far away that the phase
+// would pass 2^50, or so close to a cell that the short 1/r ends, take the
+// library's functions in a loop of their own, so that a point's value does
+// not depend on the others of its group.  MP points share a cell's loads and
+// charge: 4 where that leaves 1024 workgroups, else 1.
 template <int MP>
 __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
   __shared__ double x1[kFieldMaxN];
@@ -151,7 +157,7 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
   const int i2 = cc / n, i3 = cc - i2 * n;
   const double x2 = cell_coord(a, 1, i2), x3 = cell_coord(a, 2, i3);
   double y0[MP], s23[MP];
-  bool lib[MP], any_lib = false, all_lib = true;
+  bool lib[MP], any_lib = false, all_lib = true, own = false;
 #pragma unroll
   for (int m = 0; m < MP; ++m) {
     const int64_t pm = m0 + m < a.mb ? m0 + m : a.mb - 1;
@@ -166,7 +172,12 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
       const double u = fabs(y[d] - a.corner[d]), v = fabs(y[d] - a.corner[3 + d]);
       far2 += u > v || !(u <= v) ? u * u : v * v;
     }
-    lib[m] = !(far2 * a.kt_hi * a.kt_hi < 0x1p100 && far2 < 0x1p1000);
+    // Uniform over the wave.  With |y0| from 2^-390 on, y0 - x1 is 0 or above
+    // 2^-443, so r^2 is s23 or from kNearSq on.
+    const bool column = __any(s23[m] < kNearSq), close = __any(s23[m] > 0.0 && s23[m] < kNearSq);
+    lib[m] = !(far2 * a.kt_hi * a.kt_hi < 0x1p100 && far2 < 0x1p1000) || close ||
+             (column && fabs(y0[m]) < 0x1p-390);
+    own = own || column;
     any_lib = any_lib || lib[m];
     all_lib = all_lib && lib[m];
   }
@@ -175,7 +186,6 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
   cxd acc[MP] = {};
   // Q_p / (4 pi) of the column's cell at i1; the next cell's values are
   // loaded while the current one is summed
-  const double sg = act ? -1.0 / kFourPi : 0.0;
   const cxd* __restrict__ Dc = a.D + cc;
   const cxd* __restrict__ uc = u + cc;
   cxd dn, un;
@@ -184,13 +194,17 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
     un = uc[static_cast<int64_t>(lo) * nn];
   };
   auto next_q = [&](int i1) -> cxd {
-    const cxd q = scale(dn * un, sg);
+    const cxd q = scale(dn * un, -1.0 / kFourPi);
     const int64_t p = static_cast<int64_t>(i1 + 1 < hi ? i1 + 1 : i1) * nn;
     dn = Dc[p];
     un = uc[p];
     return q;
   };
-  if (!all_lib) {
+  auto phase = [&](double r) -> cxd {  // e^{ikr}
+    const double th = r * a.kt_hi, tl = fmadd(r, a.kt_lo, fmadd(r, a.kt_hi, -th));
+    return turn(th, tl, tab);
+  };
+  auto sum = [&](auto test_distance) {
     first_q();
     for (int i1 = lo; i1 < hi; ++i1) {
       const cxd q = next_q(i1);
@@ -199,14 +213,18 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
       for (int m = 0; m < MP; ++m) {
         const double d0 = y0[m] - x;
         const double rsq = fmadd(d0, d0, s23[m]);
-        const double safe = fmax(rsq, 0x1p-900);
-        const double ir = fast_rsqrt(safe), r = safe * ir;
-        const double th = r * a.kt_hi, tl = fmadd(r, a.kt_lo, fmadd(r, a.kt_hi, -th));
-        const cxd e = turn(th, tl, tab);
-        const cxd w = scale(q, rsq > 0.0 ? ir : 0.0);
-        acc[m] = cfma(e, w, acc[m]);
+        const bool other = !decltype(test_distance)::value || rsq >= kNearSq;
+        const double safe = other ? rsq : 1.0, ir = fast_rsqrt(safe);
+        const cxd w = scale(q, ir);
+        acc[m] = cfma(phase(safe * ir), other ? w : cxd{0.0, 0.0}, acc[m]);
       }
     }
+  };
+  if (!all_lib) {
+    if (own)
+      sum(std::true_type{});
+    else
+      sum(std::false_type{});
   }
   if (any_lib) {
 #pragma unroll
@@ -230,6 +248,11 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
       }
     }
   }
+  // lanes beyond the last column hold a copy of it
+  if (!act) {
+#pragma unroll
+    for (int m = 0; m < MP; ++m) acc[m] = cxd{0.0, 0.0};
+  }
 #pragma unroll
   for (int m = 0; m < MP; ++m) {
     if (m > 0) __syncthreads();
@@ -245,7 +268,7 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_near(FieldArgs a) {
 // is 4, or 2 or 1 where that holds every column of a smaller grid: the rest
 // would be idle lanes (n = 17: 289 columns).
 template <int MP, int COLS>
-__global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
+__global__ void __launch_bounds__(kFieldThreads, 4) k_field_far(FieldArgs a) {
   extern __shared__ __align__(16) unsigned char far_smem[];
   cxd* ph = reinterpret_cast<cxd*>(far_smem);  // [3][n][MP]
   const int n = static_cast<int>(a.n), nn = n * n;
@@ -262,21 +285,17 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
   }
   __syncthreads();
   const cxd* __restrict__ u = a.u + rhs * a.P;
+  const int c0 = cb * COLS * kFieldThreads + threadIdx.x;
   int cc[COLS];
-  double sgn[COLS];
 #pragma unroll
-  for (int j = 0; j < COLS; ++j) {
-    const int col = (cb * COLS + j) * kFieldThreads + threadIdx.x;
-    cc[j] = col < nn ? col : nn - 1;
-    sgn[j] = col < nn ? -1.0 : 0.0;
-  }
+  for (int j = 0; j < COLS; ++j) cc[j] = c0 + j * kFieldThreads < nn ? c0 + j * kFieldThreads : nn - 1;
   cxd acc[MP][COLS] = {};
   for (int i1 = lo; i1 < hi; ++i1) {
     cxd q[COLS];
 #pragma unroll
     for (int j = 0; j < COLS; ++j) {
       const int64_t p = static_cast<int64_t>(i1) * nn + cc[j];
-      q[j] = scale(a.D[p] * u[p], sgn[j]);  // Q_p
+      q[j] = scale(a.D[p] * u[p], -1.0);  // Q_p
     }
 #pragma unroll
     for (int m = 0; m < MP; ++m) {
@@ -290,8 +309,20 @@ __global__ void __launch_bounds__(kFieldThreads) k_field_far(FieldArgs a) {
     cxd t{0.0, 0.0};
 #pragma unroll
     for (int j = 0; j < COLS; ++j) {
+      if (c0 + j * kFieldThreads >= nn) continue;  // a copy of the last column
       const int i2 = cc[j] / n, i3 = cc[j] - i2 * n;
-      t = cfma(ph[(n + i2) * MP + m] * ph[(2 * n + i3) * MP + m], acc[m][j], t);
+      const cxd e = ph[(n + i2) * MP + m] * ph[(2 * n + i3) * MP + m];
+      const cxd s = acc[m][j];
+      if (isfinite(s.re) && isfinite(s.im)) {
+        t = cfma(e, s, t);
+        continue;
+      }
+      // an infinite or NaN charge, or a sum out of range: cell by cell, since
+      // the product of two sums would make infinities NaN
+      for (int i1 = lo; i1 < hi; ++i1) {
+        const int64_t p = static_cast<int64_t>(i1) * nn + cc[j];
+        t = t + (ph[i1 * MP + m] * e) * scale(a.D[p] * u[p], -1.0);
+      }
     }
     if (m > 0) __syncthreads();
     store_part(a, m0 + m < a.mb ? (rhs * a.mb + m0 + m) * a.nparts + part : -1, t);

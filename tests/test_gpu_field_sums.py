@@ -165,3 +165,57 @@ def test_sums_in_several_launches_and_with_few_columns(n, M, R):
     # more points than the scratch holds partials for, and the far field's
     # 1, 2 and 4 columns per thread at their edges (256 and 512 columns)
     test_sums_against_direct(n, M, R)
+
+
+@pytest.mark.parametrize("n,M", [(6, 3), (17, 5), (17, 4100)])
+def test_charges_out_of_range(n, M):
+    # grids with idle lanes behind the last column (36 and 289 columns).  A
+    # charge that is infinite (D u out of range, in the last column) makes
+    # infinite sums, not NaN, and the cell at the point itself is left out
+    # whatever its charge
+    k = 0.7
+    say(f"[field] n={n} M={M} charges out of range")
+    P = n ** 3
+    side = n / 2.0  # |Delta| = 1/8: D = 4 pi h / 8
+    one = torch.ones(P, dtype=torch.complex128, device="cuda")
+    X = cells(n, side, (0.0, 0.0, 0.0), 0.5)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    pts = X[torch.randint(0, P, (M,), device="cuda", generator=g)].contiguous()
+    p = (n // 2) * n * n + 5 * n + 4
+    pts[M // 2] = X[p]
+    away = (pts != X[p]).any(dim=1)
+    beta = pts - X.mean(dim=0) + torch.tensor([0.03, 0.05, 0.02], dtype=torch.float64, device="cuda")
+    beta = (beta / beta.norm(dim=1, keepdim=True)).contiguous()
+    with ori.ori_create(n, side=side) as ctx:
+        ori.ori_load(ctx, k, one, None, one)
+        base = one.clone()
+        base[p] = 0
+        ref = ori.ori_scattered_field(ctx, base, pts)
+        for bad in (complex("nan"), complex(1.7e308, 0.0)):
+            u = one.clone()
+            u[p] = bad
+            v = ori.ori_scattered_field(ctx, u, pts)
+            assert torch.equal(v[~away], ref[~away])
+            assert not torch.isfinite(torch.view_as_real(v[away])).any()
+        # the last cell of the last column: infinite sums away from it
+        u = one.clone()
+        u[P - 1] = complex(1.7e308, 0.0)
+        v = ori.ori_scattered_field(ctx, u, pts[away] + 0.25)
+        assert torch.isinf(torch.view_as_real(v)).all()
+        A = ori.ori_far_field(ctx, u, beta)
+        ph = k * (X[P - 1] * beta).sum(dim=1)
+        clear = (ph.sin().abs() > 1e-3) & (ph.cos().abs() > 1e-3)
+        assert clear.any() and torch.isinf(torch.view_as_real(A[clear])).all()
+
+
+def test_distances_far_below_one():
+    # squares below 2^-900, where the short form of 1 / r ends
+    say("[field] distances of 1e-140 and 1e-100")
+    one = torch.ones(1, dtype=torch.complex128, device="cuda")
+    r = torch.tensor([1e-140, 3e-136, 1e-100, 1e-3], dtype=torch.float64)
+    x = torch.zeros(4, 3, dtype=torch.float64)
+    x[:, 0] = r
+    with ori.ori_create(1, cell_offset=0.0) as ctx:
+        ori.ori_load(ctx, 1.0, one, None, one)
+        v = ori.ori_scattered_field(ctx, one, x.cuda()).cpu()
+    assert torch.allclose(v.abs(), 1.0 / r, rtol=1e-14, atol=0)
