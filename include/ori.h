@@ -115,8 +115,8 @@ typedef struct {
                             measured faster than a replay.                        */
   int32_t multi;         /* ori_group_solve: 1 runs the COCG iterations of the
                             problems still running in one launch per kernel when
-                            every one of them has a padded length up to 256
-                            and the default layout, and neither
+                            every one of them has a padded length of 8 to 256
+                            and the default tiles and Z plan, and neither
                             per-kernel profiling nor the guard checks of
                             ORI_CHECK_GUARDS=1 are on (otherwise, and with 0,
                             each problem launches its own kernels).  The
@@ -317,13 +317,16 @@ ori_status ori_charges(ori_ctx ctx, const void* u, void* q);
  * field.  A cell point at distance exactly 0 is left out, as in the sum of
  * eq. 2.19, so at the cell points u0 + v reproduces u.  x: device
  * double[M][3]; v: device complex128[nrhs][M].  Direct sum in FP64, O(M P)
- * work, deterministic.  Synchronises the context stream. */
+ * work, deterministic: a value does not depend on the other points of the
+ * call, but its last bits may depend on their number M and on nrhs, by which
+ * the sum over the cells is split.  Synchronises the context stream. */
 ori_status ori_scattered_field(ori_ctx ctx, const void* u, const double* x, int64_t M, void* v);
 
 /* Far-field amplitude A(beta) = (1 / 4 pi) sum_p exp(-i k beta . x_p) q_p,
  * so that v(r beta) = A(beta) e^{ikr} / r + O(1/r^2) as r -> infinity.
  * beta: device double[M][3] unit directions; A: device complex128[nrhs][M].
- * Synchronises the context stream. */
+ * The last bits depend on M and nrhs as above.  Synchronises the context
+ * stream. */
 ori_status ori_far_field(ori_ctx ctx, const void* u, const double* beta, int64_t M, void* A);
 
 /* Refraction recipe on the grid (P entries each; ctx supplies P, the stream

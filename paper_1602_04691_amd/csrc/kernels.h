@@ -44,9 +44,11 @@ enum : int32_t {
   FLAG_BAD_COEFF = 32,     // NaN / Inf in h or N, or N < 0, met in ori_load (sc[0])
   FLAG_CONVERGED = 16,     // rr <= rr_target
 };
-// A right-hand side with one of these flags is frozen: every kernel of a COCG
-// iteration skips it, so an iteration launched after the last one needed
+// A right-hand side with one of these flags is frozen: the kernels of a COCG
+// iteration skip it, so an iteration launched after the last one needed
 // (the host reads the flags one block of iterations late) changes nothing.
+// Only the Z pass of a batch does not test the flags: it transforms what the
+// work array B holds for a frozen one, which nothing reads (I2 skips it).
 // alpha keeps the value of its last iteration for the step x += alpha p that
 // is still pending (k_x_flush).
 constexpr int32_t FLAG_DONE = FLAG_BREAKDOWN_RHO | FLAG_BREAKDOWN_MU | FLAG_ZERO_RESIDUAL | FLAG_CONVERGED;

@@ -152,10 +152,11 @@ constexpr int L = 216;
 
 // The lengths of this translation unit: every length with multi-problem
 // bodies (multi_length in kernels.h), or the reserved ones alone.  The
-// radix 10 and 12 stages of the lengths between them need more registers
-// (complex128 F2 104 instead of 80), which every workgroup of a launch
-// pays for, so a set of problems without such a length runs kernels
-// without their bodies (n = 19 and 83 in complex128: 3.0 vs 3.5 ms).
+// lengths between them need more registers (complex128 I1 114 instead of 90,
+// I2 116 instead of 78, Z 172 instead of 152), which every workgroup of a
+// launch pays for, so a set of problems without such a length runs kernels
+// without their bodies (complex128, n = 32, 48, 64, 96: 4.02 vs 4.11 ms, n =
+// 48, 96 twice 5.68 vs 5.80 ms).
 #define ORI_MULTI_RESERVED(X) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96) X(128) X(192) X(256)
 #if ORI_MULTI_ALL
 #define ORI_MULTI_LENGTHS(X) ORI_MULTI_RESERVED(X) X(72) X(100) X(108) X(144) X(160) X(200) X(216)
@@ -178,10 +179,16 @@ constexpr int max_threads() {
   return t;
 }
 
-// Waves per SIMD that the kernels with the lengths between the reserved ones
-// keep, as the kernels without them have by themselves: complex128 Z three
-// (it would take 174 registers and leave two), the other passes five (104 to
-// 116, four).
+// Waves per SIMD that the complex128 kernels with the lengths between the
+// reserved ones keep: Z three, the other passes five.  By themselves they
+// take 172 (Z, two waves) and 104 to 116 registers (four); held, they spill 2
+// and 40 to 58.  Neither is better for all sets (ms, held and without a
+// spill: four n = 72 5.07 and 4.68, n = 33, 50, 70, 100 6.12 and 5.88, n = 100
+// twice 6.46 and 6.48, eight n = 36 3.49 and 3.64, n = 54, 80, 108 6.88 and
+// 7.28).  The kernels without those lengths keep what they take, F1 116 and
+// F2 100 (L = 96 as 8 x 12, four waves): five waves there, by spilling or
+// with L = 96 as 8 x 4 x 3, are within 1 % (n = 32, 48, 64, 96 4.02 and 4.01
+// to 4.04), and 8 x 4 x 3 is slower alone (n = 48 product 42.3 vs 43.9 us).
 template <typename T, int PASS>
 constexpr int multi_min_waves() {
   return ORI_MULTI_ALL && sizeof(T) == 8 ? (PASS == MP_Z ? 3 : 5) : 1;

@@ -780,7 +780,8 @@ ori_status shared_twiddles(int device, int64_t L, cxd** twd, cxf** twf) {
 // COCG on (I + S G0 S) w = rhs for every right-hand side in lockstep,
 // vectors of type prec (FFTs too).  Expects x, r initialised and FIN_INIT
 // done (per right-hand side targets set); a right-hand side that converges
-// or breaks down is frozen on the device (alpha = 0) while the others go on.
+// or breaks down is frozen on the device while the others go on: kernels skip
+// it (FLAG_DONE), and its alpha stays for the step still pending (flush_x).
 // ---------------------------------------------------------------------------
 
 bool all_done(ori_ctx c) {
@@ -1130,8 +1131,8 @@ ori_status sync_members(const Members& ms) {
 // Expects each member's x, r initialised and FIN_INIT done.  Member i runs
 // at most budget[i] iterations and leaves when all its right-hand sides are
 // done (a right-hand side that converges or breaks down is frozen on the
-// device, alpha = 0, while the others of its context go on); ran[i]
-// receives the iterations it ran.  Each member runs exactly the kernels of
+// device, as above, while the others of its context go on); ran[i] receives
+// the iterations it ran.  Each member runs exactly the kernels of
 // its own solve, so results do not depend on the other members.
 //
 // The host reads the scalars of a block while the next one runs: block k + 1
@@ -1189,8 +1190,10 @@ ori_status group_cocg(const Members& ms, int prec, const std::vector<int>& budge
     b->one_stream = mset || active.size() == 1;
     // Several members with launches of their own replay a graph with a chain
     // each.  Where one stream runs the block, plain launches are faster than
-    // a replay (about 12 us less per iteration: n = 32 solve 0.99 -> 0.81 ms,
-    // n = 128 5.0 -> 4.8 ms), because the host is a block ahead.
+    // a replay: about 12 us less per iteration where the host is a block ahead
+    // (n = 32 solve 0.99 -> 0.81 ms, n = 128 5.0 -> 4.8 ms), and 0.2 to 0.3 ms
+    // less per solve beyond kAheadCells, where it waits (n = 210 24.73 -> 24.50
+    // ms, n = 256 33.71 -> 33.48 ms, mixed 24.46 -> 24.20 ms).
     hipGraphExec_t exec = nullptr;
     if (use_graph && !b->one_stream && b->blk == check_every)
       ORI_TRY(iteration_graph(active, prec, b->blk, it == 0, cache, &exec));
@@ -1370,9 +1373,11 @@ int default_blk_lg(ori_ctx c, int f) {
 // but a complex64 batch at L <= 128 wide (n = 64 with 32 right-hand sides
 // 0.107 vs 0.136 ms: the pass is bound by memory there, and wide tiles move
 // 128-byte rows).  The lengths between the reserved ones from L = 576 on:
-// complex128 wide (128-byte rows; n = 360 5.24 vs 6.37 ms, n = 320 3.65 vs
-// 3.73 ms), complex64 narrow where narrow tiles are whole wavefronts (n =
-// 320 2.06 vs 2.35 ms, but n = 360 3.10 vs 2.88 ms).
+// complex128 wide (128-byte rows), complex64 narrow where narrow tiles are
+// whole wavefronts (L = 640 and 768).  One product, wide and narrow, ms:
+//   n            288         300         320         340         360         370         384
+//   complex128   2.55 2.60   3.11 3.17   3.29 3.39   4.77 6.09   5.03 6.39   5.83 6.22   5.77 6.10
+//   complex64    1.48 1.52   2.11 1.92   2.22 1.92   2.66 2.85   2.69 2.89   3.64 3.48   3.80 3.62
 int default_znarrow(ori_ctx c, int f) {
   const int L = static_cast<int>(c->L);
   if (f == 1 && L <= 128 && c->nrhs >= 8) return 0;

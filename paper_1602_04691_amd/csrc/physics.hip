@@ -24,8 +24,8 @@
 // points, and walks i1.  What depends on the column alone is computed once
 // per column, what depends on the cell alone (its charge) once for all the
 // points, and what depends on the point and i1 alone is uniform or read from
-// LDS.  4 096 points and n = 64 on one MI355X: the field 4.28 -> 1.70 ms
-// (120 -> about 43 issue slots per pair), the far field 1.44 -> 0.41 ms.
+// LDS.  4 096 points and n = 64 on one MI355X: the field 4.28 -> 1.38 ms
+// (120 -> about 39 issue slots per pair), the far field 1.44 -> 0.34 ms.
 #include "cx.h"
 #include "kernels.h"
 #include "launch.h"

@@ -164,7 +164,19 @@ constexpr int most_butterflies(int L, const RadixPlan& p) {
 // the largest count where the counts lie close together (L = 640: 80, 64,
 // 80): one butterfly per thread and stage holds half the registers of a
 // second, mostly empty round, and the threads without a butterfly are whole
-// wavefronts of the strided passes, which skip the stage.
+// wavefronts of the strided passes, which skip the stage.  Exceptions (one
+// product, us; R right-hand sides):
+//  - L = 160 (40, 16, 40) takes 20, between 16 and 40: n = 80 complex128 81.9
+//    against 77.8 (16) and 82.0 (40), complex64 53.9 against 55.5 and 55.5, n =
+//    75 76.4, 76.7, 80.0 and 53.4, 56.1, 54.4, n = 80 with R = 8 401, 393, 454
+//    and 201, 205, 223.
+//  - L = 80 and 96 take L / 8 and not 8, which keeps the Z tile for both of
+//    their plans: n = 40 36.1 against 38.3 and 32.8 against 34.3 (R = 8 70.8
+//    against 67.7 and 47.8 against 49.3), n = 48 41.9 against 43.8 and 35.7
+//    against 37.0 (R = 8 86.2 against 94.2 and 60.2 against 62.3).
+//  - L = 320 (40, 64, 40) takes 40: complex64 is 1 % faster than on 64 (n = 160
+//    222 against 225), complex128 7 % slower (442 against 412), and both share
+//    the count.
 constexpr int threads_per_pencil(int L, int variant = 0) {
   const RadixPlan p = radix_plan(L, variant);
   if (L == 160) return 20;  // 40, 16, 40
