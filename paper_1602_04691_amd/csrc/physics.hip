@@ -25,7 +25,7 @@
 // per column, what depends on the cell alone (its charge) once for all the
 // points, and what depends on the point and i1 alone is uniform or read from
 // LDS.  4 096 points and n = 64 on one MI355X: the field 4.28 -> 1.38 ms
-// (120 -> about 39 issue slots per pair), the far field 1.44 -> 0.34 ms.
+// (120 -> 38 issue slots per pair), the far field 1.44 -> 0.34 ms.
 #include "cx.h"
 #include "kernels.h"
 #include "launch.h"
@@ -77,7 +77,7 @@ constexpr int kFieldMaxN = 512;
 // cancel against those of other workgroups, so the rounding of the last few
 // additions would show: their errors are kept.  Error of the field at points
 // around a body of n = 64 against long double: 1.0e-16 (k = 5) and 0.8e-16
-// (k = 8), 3.6e-16 and 5.8e-16 without; the time is the same (1.86 ms).
+// (k = 8), 3.6e-16 and 5.8e-16 without, in the same time.
 __device__ __forceinline__ void store_part(const FieldArgs& a, int64_t at, cxd v) {
   cxd lo{0.0, 0.0};
   const cxd s = block_sum_cx(v, &lo);
